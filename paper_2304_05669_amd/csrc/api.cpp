@@ -191,7 +191,7 @@ int fipt_scene_create(const float* verts, int64_t n_verts, const int32_t* tris, 
         (rc = dev_alloc(&s->d_rad, bvh.tris.size(), &s->bytes)) ||
         (rc = dev_alloc(&s->d_order, bvh.order.size(), &s->bytes)) ||
         (rc = dev_alloc(&s->d_tri_idx, (size_t)(3 * n_tris), &s->bytes)) ||
-        (rc = dev_alloc(&s->d_counters, (size_t)kBakeSlots * kXcdCount, &s->bytes)) ||
+        (rc = dev_alloc(&s->d_counters, (size_t)kBakeSlots * kCounterInts, &s->bytes)) ||
         (rc = dev_alloc(&s->d_leaf_of, (size_t)n_tris, &s->bytes)) ||
         (rc = dev_alloc(&s->d_emit, (size_t)n_tris + 1, &s->bytes)) ||
         (rc = dev_alloc(&s->d_emit_blocks, (size_t)((n_tris + 255) / 256), &s->bytes))) {
@@ -475,7 +475,7 @@ static int bake_common(fipt_scene s, const fipt_points* pts, const fipt_bake_par
     hipStream_t st = (hipStream_t)stream;
     hipError_t e = hipStreamWaitEvent(st, s->slot_done[k], 0);
     if (e != hipSuccess) return fail(FIPT_EHIP, "bake slot wait: %s", hipGetErrorString(e));
-    rc = launch_bake(b, s->d_counters + (size_t)k * kXcdCount, stats, stream);
+    rc = launch_bake(b, s->d_counters + (size_t)k * kCounterInts, stats, stream);
     if (rc) return rc;
     e = hipEventRecord(s->slot_done[k], st);
     if (e != hipSuccess) return fail(FIPT_EHIP, "bake slot event: %s", hipGetErrorString(e));
@@ -548,7 +548,7 @@ int fipt_refine(fipt_scene s, const fipt_points* pts, const fipt_bake_params* p,
         s->next_slot = (k + 1) % kBakeSlots;
         e = hipStreamWaitEvent(st, s->slot_done[k], 0);
         if (e != hipSuccess) return fail(FIPT_EHIP, "refine slot wait: %s", hipGetErrorString(e));
-        rc = launch_refine(b, rl, s->d_counters + (size_t)k * kXcdCount, stream);
+        rc = launch_refine(b, rl, s->d_counters + (size_t)k * kCounterInts, stream);
         if (rc) return rc;
         e = hipEventRecord(s->slot_done[k], st);
         if (e != hipSuccess) return fail(FIPT_EHIP, "refine slot event: %s", hipGetErrorString(e));

@@ -28,6 +28,7 @@ using dev::V3;
 using dev::v3;
 using dev::lobe_of;
 using dev::next_point;
+using dev::point_queue;
 using dev::slot_plane;
 using dev::wave_uniform;
 
@@ -439,9 +440,8 @@ __global__ __launch_bounds__(kBlock) FIPT_BAKE_OCCUPANCY void k_bake(BakeLaunch 
     int32_t* stack = s_stack + threadIdx.x;
     uint32_t n_rays = 0, n_nodes = 0, n_tris = 0, n_hits = 0, n_node_steps = 0, n_tri_steps = 0,
              n_chain = 0;
-    const int home = (int)(blockIdx.x % kXcdCount);   // the XCD this workgroup runs on
-    int tried = 0;
-    for (int64_t p; (p = next_point(counters, home, tried, b.n, lane)) >= 0;) {
+    uint32_t queue = point_queue(b.n, lane);
+    for (int64_t p; (p = next_point(queue, counters, b.n, lane)) >= 0;) {
         if (REFILL)
             bake_point_refill<COUNT, VOXEL>(b, b.sigma, p, lane, stack, n_rays, n_nodes, n_tris, n_hits,
                                      n_node_steps, n_tri_steps, n_chain);
@@ -501,9 +501,8 @@ __global__ __launch_bounds__(kBlock) FIPT_BAKE_OCCUPANCY void k_bake_tiles(const
     int32_t* stack = s_stack + threadIdx.x;
     uint32_t a = 0, bb = 0, c = 0, d = 0, e = 0, f = 0, g = 0;   // counters, unused here
     const int64_t total = tiles[n_tiles - 1].first + tiles[n_tiles - 1].job.n;
-    const int home = (int)(blockIdx.x % kXcdCount);       // the XCD this workgroup runs on
-    int tried = 0;
-    for (int64_t p; (p = next_point(counters, home, tried, total, lane)) >= 0;) {
+    uint32_t queue = point_queue(total, lane);
+    for (int64_t p; (p = next_point(queue, counters, total, lane)) >= 0;) {
         // last tile whose first point is <= p
         int lo = 0, hi = n_tiles - 1;
         while (lo < hi) {
@@ -552,7 +551,7 @@ __global__ void k_lobe_uniforms(uint64_t seed, int64_t p0, int64_t total, int32_
 }
 
 __global__ void k_zero_counters(int32_t* counters) {
-    if (threadIdx.x < kXcdCount) counters[threadIdx.x] = 0;
+    if (threadIdx.x < kXcdCount) counters[threadIdx.x * kCounterStride] = 0;
 }
 
 __global__ void k_set_radiance(TriRad* rad, const int32_t* order, const int32_t* tri_idx,
@@ -696,6 +695,15 @@ int launch_lobe_uniforms(uint64_t seed, int64_t p0, int64_t n_points, int32_t lo
     return check_launch("lobe_uniforms");
 }
 
+void zero_point_counters(int32_t* counters, int64_t n, int64_t blocks, void* stream) {
+    // (a kernel, not a memset node, so a caller may capture the call)
+    for (int x = 0; x < kXcdCount; ++x)
+        if (n * (x + 1) / kXcdCount - n * x / kXcdCount > (blocks - x + kXcdCount - 1) / kXcdCount) {
+            hipLaunchKernelGGL(k_zero_counters, dim3(1), dim3(64), 0, (hipStream_t)stream, counters);
+            return;
+        }
+}
+
 int launch_bake(const BakeLaunch& b, int32_t* counters, uint64_t* stats, void* stream) {
     // persistent grid: up to one round of resident workgroups, a multiple
     // of kXcdCount so every XCD gets the same number of workgroups
@@ -704,8 +712,7 @@ int launch_bake(const BakeLaunch& b, int32_t* counters, uint64_t* stats, void* s
     blocks = std::max<int64_t>(kXcdCount, (blocks + kXcdCount - 1) / kXcdCount * kXcdCount);
     const dim3 grid((unsigned)blocks), block(kBlock);
     hipStream_t st = (hipStream_t)stream;
-    // zeroed by a kernel, not a memset node, so a caller may capture the call
-    hipLaunchKernelGGL(k_zero_counters, dim3(1), dim3(64), 0, st, counters);
+    zero_point_counters(counters, b.n, blocks, stream);
     const bool refill = b.K <= kRefillMaxK;
     if (b.sc.vox) {
         // radiance from the voxel cache (Sec. 4.2)

@@ -188,7 +188,7 @@ struct BakeLaunch {
     uint64_t seed;
     float eps;
 };
-// counters_dev: kXcdCount int32 point counters owned by this launch; the
+// counters_dev: kCounterInts int32 of point counters owned by this launch; the
 // launcher zeroes them on `stream` before the kernel.
 int launch_bake(const BakeLaunch& b, int32_t* counters_dev, uint64_t* stats, void* stream);
 
@@ -214,13 +214,20 @@ int launch_refine(const BakeLaunch& b, const RefineLaunch& r, int32_t* counters,
 // MI355X has 8 XCDs (dies, each with its own L2); the dispatcher places
 // workgroup i of a launch on XCD i % kXcdCount.
 constexpr int kXcdCount = 8;
+// The point counters of a launch, one per XCD, each in a 256-byte line of its
+// own (see next_point).
+constexpr int kCounterStride = 64;
+constexpr int kCounterInts = kXcdCount * kCounterStride;
+// Zero the counters of a launch of `blocks` one-wave workgroups over n points
+// (nothing to do when every wavefront's first point covers them all).
+void zero_point_counters(int32_t* counters_dev, int64_t n, int64_t blocks, void* stream);
 
 // Serving: a tile is a contiguous run of one request's points.
 struct TileDesc {
     BakeLaunch job;       // job.n = points in the tile, pointers already offset
     int64_t first;        // points of all earlier tiles in the launch
 };
-// counters_dev: kXcdCount zeroed int32 counters.
+// counters_dev: kCounterInts zeroed int32.
 int launch_bake_tiles(const TileDesc* tiles_dev, int32_t n_tiles, int32_t* counters_dev,
                       int32_t grid, void* stream);
 int bake_tiles_grid_hint();
@@ -337,7 +344,7 @@ struct fipt_scene_s {
     hipEvent_t refine_done = nullptr;  // last refinement's completion (it rewrites d_emit)
     std::mutex refine_mu;
     int32_t* d_tri_idx = nullptr;  // original [T][3] vertex indices
-    int32_t* d_counters = nullptr;  // [kBakeSlots][kXcdCount]
+    int32_t* d_counters = nullptr;  // [kBakeSlots][kCounterInts]
     hipEvent_t slot_done[kBakeSlots] = {};
     int next_slot = 0;
     std::mutex slot_mu;

@@ -33,7 +33,14 @@ using dev::V3;
 using dev::v3;
 
 constexpr int kBlock = 64;
+// The wavefronts a CU holds at once (4 per SIMD): every wavefront starts with
+// a point of its own, so a workgroup that waited for a place would keep its
+// point until the others are nearly done.  Four per SIMD (128 VGPRs, two of
+// them spilled) measured faster than three (131, none) and five (96, 44
+// spilled): 34.6 against 42.3 and 39.1 ms on 76,800 points of the room at 64
+// samples per lobe.
 constexpr int kGridWavesPerCu = 16;
+#define FIPT_REFINE_OCCUPANCY __attribute__((amdgpu_waves_per_eu(4, 8)))
 constexpr int kListBlock = 256;        // triangles per block of the emitter compaction
 constexpr int kScanThreads = 1024;
 
@@ -820,21 +827,16 @@ __device__ void refine_point_spec(const RefineArgs& A, int64_t p, int lane, int3
 // The chunked layout (any K) or the per-lane paths (K <= kRefillMaxK), one
 // instance each, so that each gets its own register allocation.
 template <bool CHUNKED>
-__global__ __launch_bounds__(kBlock) void k_refine(RefineArgs A, int32_t* counters) {
+__global__ __launch_bounds__(kBlock) FIPT_REFINE_OCCUPANCY void k_refine(RefineArgs A, int32_t* counters) {
     __shared__ int32_t s_stack[kStackSize * kBlock];
     const int lane = threadIdx.x & 63;
     int32_t* stack = s_stack + threadIdx.x;
     const int n_emit = __builtin_amdgcn_readfirstlane(*A.n_emit);
-    const int home = (int)(blockIdx.x % kXcdCount);
-    int tried = 0;
-    for (int64_t p; (p = dev::next_point(counters, home, tried, A.b.n, lane)) >= 0;) {
+    uint32_t queue = dev::point_queue(A.b.n, lane);
+    for (int64_t p; (p = dev::next_point(queue, counters, A.b.n, lane)) >= 0;) {
         if (CHUNKED) refine_point(A, p, lane, stack, n_emit);
         else refine_point_spec(A, p, lane, stack, n_emit);
     }
-}
-
-__global__ void k_zero_counters_r(int32_t* counters) {
-    if (threadIdx.x < kXcdCount) counters[threadIdx.x] = 0;
 }
 
 int check(const char* what) {
@@ -878,7 +880,7 @@ int launch_refine(const BakeLaunch& b, const RefineLaunch& r, int32_t* counters,
     int64_t blocks = std::min<int64_t>(b.n, (int64_t)cus * kGridWavesPerCu);
     blocks = std::max<int64_t>(kXcdCount, (blocks + kXcdCount - 1) / kXcdCount * kXcdCount);
     hipStream_t st = (hipStream_t)stream;
-    hipLaunchKernelGGL(k_zero_counters_r, dim3(1), dim3(64), 0, st, counters);
+    zero_point_counters(counters, b.n, blocks, stream);
     // the per-lane paths give every output slot its own lane (3 + 6K <= 64)
     if (A.b.K <= kRefillMaxK)
         hipLaunchKernelGGL(k_refine<false>, dim3((unsigned)blocks), dim3(kBlock), 0, st, A, counters);

@@ -66,7 +66,7 @@ struct TileRec {
 struct Slot {
     TileDesc* host = nullptr;   // pinned
     TileDesc* dev = nullptr;
-    int32_t* counter = nullptr;   // kXcdCount point counters
+    int32_t* counter = nullptr;   // kCounterInts of point counters
     hipStream_t stream = nullptr;
     hipEvent_t done = nullptr;
     bool busy = false;
@@ -274,7 +274,7 @@ struct fipt_server_s {
                 hipError_t e = hipMemcpyAsync(s.dev, s.host, sizeof(TileDesc) * nt,
                                               hipMemcpyHostToDevice, s.stream);
                 if (e == hipSuccess)
-                    e = hipMemsetAsync(s.counter, 0, sizeof(int32_t) * kXcdCount, s.stream);
+                    e = hipMemsetAsync(s.counter, 0, sizeof(int32_t) * kCounterInts, s.stream);
                 int rc = e == hipSuccess ? launch_bake_tiles(s.dev, nt, s.counter, grid, s.stream)
                                          : FIPT_EHIP;
                 if (rc == FIPT_OK) e = hipEventRecord(s.done, s.stream);
@@ -349,7 +349,7 @@ int fipt_server_create(int32_t device, int64_t pool_bytes, int32_t max_inflight,
             e = hipHostMalloc(reinterpret_cast<void**>(&sl.host), sizeof(TileDesc) * max_inflight, 0);
         if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void**>(&sl.dev), sizeof(TileDesc) * max_inflight);
         if (e == hipSuccess)
-            e = hipMalloc(reinterpret_cast<void**>(&sl.counter), sizeof(int32_t) * kXcdCount);
+            e = hipMalloc(reinterpret_cast<void**>(&sl.counter), sizeof(int32_t) * kCounterInts);
         if (e == hipSuccess) e = hipEventCreateWithFlags(&sl.done, hipEventDisableTiming);
     }
     if (e != hipSuccess) {
