@@ -133,6 +133,17 @@ __device__ __forceinline__ void swap_halves(float x, float y, float& lo_pair, fl
     hi_pair = __uint_as_float(r[1]);
 }
 
+// The weights of all three layers into LDS (rows of kWs floats for W1, W2).
+__device__ __forceinline__ void load_weights(const float* __restrict__ params, float* w) {
+    const float* src = params + kTable;
+    for (int q = threadIdx.x; q < kW1 + kW2; q += kBlock) {
+        const int m = q / kW1, rc = q % kW1;
+        w[m * kHid * kWs + (rc / kIn) * kWs + rc % kIn] = src[q];
+    }
+    for (int q = threadIdx.x; q < kW3; q += kBlock) w[2 * kHid * kWs + q] = src[kW1 + kW2 + q];
+    __syncthreads();
+}
+
 // SAVED: the workspace already holds the encoding (rows 0-63, written by
 // the forward pass of the same parameters and points), which is read
 // instead of gathered from the tables again.
@@ -141,15 +152,7 @@ __global__ __launch_bounds__(kBlock) void k_hg_backward(HgArgs a, const float* _
                                                              int64_t gs, float* __restrict__ ws,
                                                              int64_t wn, float2* __restrict__ fgrad) {
     __shared__ float w[kLdsW];
-    {
-        const float* src = a.params + kTable;
-        for (int q = threadIdx.x; q < kW1 + kW2; q += kBlock) {
-            const int m = q / kW1, rc = q % kW1;
-            w[m * kHid * kWs + (rc / kIn) * kWs + rc % kIn] = src[q];
-        }
-        for (int q = threadIdx.x; q < kW3; q += kBlock) w[2 * kHid * kWs + q] = src[kW1 + kW2 + q];
-    }
-    __syncthreads();
+    load_weights(a.params, w);
     const float* W1 = w;                   // W1[o][c] at o * kWs + c
     const float* W2 = w + kHid * kWs;      // W2[o][c] at o * kWs + c
     const float* W3 = w + 2 * kHid * kWs;  // W3[o][c] at o * 64 + c
@@ -356,21 +359,11 @@ __global__ __launch_bounds__(kBlock) void k_hg_backward(HgArgs a, const float* _
 
 // The forward pass in the same layout: the two hidden layers on the matrix
 // cores, the five outputs summed per half-wave on the vector ALUs.
-// SAVE: the encoding also goes to rows 0-63 of the backward pass's
-// workspace ws[.][wn], so that the backward pass need not gather it again.
-template <bool SAVE>
-__global__ __launch_bounds__(kBlock) void k_hg_forward(HgArgs a, float* __restrict__ out, int64_t os,
-                                                       float* __restrict__ ws, int64_t wn) {
+// For callers without room for the encoding; k_hg_encode and k_hg_mlp, which
+// keep it, take 1.2 against 1.67 ms on 1,843,200 points.
+__global__ __launch_bounds__(kBlock) void k_hg_forward(HgArgs a, float* __restrict__ out, int64_t os) {
     __shared__ float w[kLdsW];
-    {
-        const float* src = a.params + kTable;
-        for (int q = threadIdx.x; q < kW1 + kW2; q += kBlock) {
-            const int m = q / kW1, rc = q % kW1;
-            w[m * kHid * kWs + (rc / kIn) * kWs + rc % kIn] = src[q];
-        }
-        for (int q = threadIdx.x; q < kW3; q += kBlock) w[2 * kHid * kWs + q] = src[kW1 + kW2 + q];
-    }
-    __syncthreads();
+    load_weights(a.params, w);
     const float* W1 = w;
     const float* W2 = w + kHid * kWs;
     const float* W3 = w + 2 * kHid * kWs;
@@ -402,10 +395,6 @@ __global__ __launch_bounds__(kBlock) void k_hg_forward(HgArgs a, float* __restri
                     e0 = fmaf(wt[k], v.x, e0);
                     e1 = fmaf(wt[k], v.y, e1);
                 }
-            }
-            if (SAVE && live) {
-                ws[(int64_t)(2 * l) * wn + i] = e0;
-                ws[(int64_t)(2 * l + 1) * wn + i] = e1;
             }
             float b0, b1;
             swap_halves(e0, e1, b0, b1);
@@ -451,6 +440,158 @@ __global__ __launch_bounds__(kBlock) void k_hg_forward(HgArgs a, float* __restri
         float pa, pb;
         swap_halves(s0, s1, pa, pb);
         if (live) out[o * os + i] = 1.0f / (1.0f + expf(-(pa + pb)));
+    }
+}
+
+// ---- the encoding as a kernel of its own ------------------------------------
+// One level of one point per thread, into rows 2l and 2l + 1 of ws[.][wn], all
+// points of a level before the next (the grid's y).  What
+// bounds the gathers is where a level's 4 MB table is found: with every
+// wavefront going through all 32 levels (k_hg_forward) the tables in use at
+// once are the whole 134 MB, and each 8-byte entry brings a line from beyond
+// the L2, 6 KB per point.  One level at a time fits each XCD's 4 MB L2 (91 %
+// of the requests hit), and what is left is the L2's rate of requests, about
+// 85 per point: 0.91 ms on the room's 1,843,200 points in camera order (0.94
+// with a level's points on one XCD only: the levels are not equal; 1.00 with
+// non-temporal positions and stores), against 1.72 ms for all of
+// k_hg_forward's gathers and products, with the encoding kept.
+// PAIR: vertices x and x + 1 of an even x differ in the lowest bit of the
+// slot only (the hash multiplies x by 1), so one 16-byte load brings both;
+// for an odd x the second is loaded apart (6 requests per cell instead of 8).
+// Needs the parameters 16-byte aligned.
+template <bool PAIR>
+__global__ __launch_bounds__(kBlock) void k_hg_encode(HgArgs a, float* __restrict__ ws,
+                                                      int64_t wn) {
+    const int l = (int)blockIdx.y;
+    const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    if (i >= a.n) return;
+    float p[3];
+    unit_pos(a, i, p);
+    uint32_t idx[8];
+    float wt[8];
+    corners(l, p, idx, wt);
+    const float2* t = reinterpret_cast<const float2*>(a.params) + (int64_t)l * kT;
+    float2 v[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) v[q] = make_float2(0.0f, 0.0f);
+    if (PAIR) {
+#pragma unroll
+        for (int q = 0; q < 8; q += 2) {
+            const bool both = (idx[q] ^ 1u) == idx[q + 1];
+            if (wt[q] != 0.0f || (both && wt[q + 1] != 0.0f)) {
+                const float4 f = *reinterpret_cast<const float4*>(t + (idx[q] & ~1u));
+                const float2 even = make_float2(f.x, f.y), odd = make_float2(f.z, f.w);
+                v[q] = (idx[q] & 1u) ? odd : even;
+                v[q + 1] = (idx[q] & 1u) ? even : odd;
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < 8; q += 2)
+            if ((idx[q] ^ 1u) != idx[q + 1] && wt[q + 1] != 0.0f) v[q + 1] = t[idx[q + 1]];
+    } else {
+#pragma unroll
+        for (int q = 0; q < 8; ++q)
+            if (wt[q] != 0.0f) v[q] = t[idx[q]];
+    }
+    float e0 = 0.0f, e1 = 0.0f;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+        if (wt[q] != 0.0f) {
+            e0 = fmaf(wt[q], v[q].x, e0);
+            e1 = fmaf(wt[q], v[q].y, e1);
+        }
+    }
+    ws[(int64_t)(2 * l) * wn + i] = e0;
+    ws[(int64_t)(2 * l + 1) * wn + i] = e1;
+}
+
+// The layers of k_hg_forward on an encoding read from ws (same products in
+// the same order, so the same bits): a persistent grid, each wavefront taking
+// 64 points at a time, the weights read into LDS once per workgroup.  Bound by
+// the single-precision matrix rate: 256 products of 64 cycles per wavefront
+// and tile are 0.19 ms on the room's 1,843,200 points; it takes 0.32.
+constexpr int kMlpAhead = 4;   // levels whose features are in flight
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3, 8))) void k_hg_mlp(const float* __restrict__ params,
+                                                   const float* __restrict__ ws, int64_t wn, int64_t n,
+                                                   float* __restrict__ out, int64_t os) {
+    __shared__ float w[kLdsW];
+    load_weights(params, w);
+    const float* W1 = w;
+    const float* W2 = w + kHid * kWs;
+    const float* W3 = w + 2 * kHid * kWs;
+    const int lane = threadIdx.x & 63, h = lane >> 5, lo = lane & 31;
+    const int64_t step = (int64_t)gridDim.x * kBlock;
+    for (int64_t base = (int64_t)blockIdx.x * kBlock + (threadIdx.x & ~63); base < n; base += step) {
+        const int64_t i = base + lane;
+        const bool live = i < n;
+        const float* src = ws + (live ? i : 0);
+        asm volatile("" ::: "memory");   // (the weights are read from LDS where they are used)
+        v16f z[2][2];
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) z[u][j][r] = 0.0f;
+        // the next levels' features are in flight while these are multiplied
+        float e[2 * kMlpAhead], en[2 * kMlpAhead];
+#pragma unroll
+        for (int q = 0; q < 2 * kMlpAhead; ++q) en[q] = src[(int64_t)q * wn];
+#pragma unroll 1
+        for (int l0 = 0; l0 < kLevels; l0 += kMlpAhead) {
+#pragma unroll
+            for (int q = 0; q < 2 * kMlpAhead; ++q) e[q] = en[q];
+            const float* nx = src + (int64_t)(2 * min(l0 + kMlpAhead, kLevels - kMlpAhead)) * wn;
+#pragma unroll
+            for (int q = 0; q < 2 * kMlpAhead; ++q) en[q] = nx[(int64_t)q * wn];
+#pragma unroll
+            for (int q = 0; q < kMlpAhead; ++q) {
+                const float e0 = live ? e[2 * q] : 0.0f, e1 = live ? e[2 * q + 1] : 0.0f;
+                float b0, b1;
+                swap_halves(e0, e1, b0, b1);
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    const float av = W1[(32 * u + lo) * kWs + 2 * (l0 + q) + h];
+                    z[u][0] = mfma2(av, b0, z[u][0]);
+                    z[u][1] = mfma2(av, b1, z[u][1]);
+                }
+            }
+        }
+        v16f y[2][2];
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) y[u][j][r] = 0.0f;
+#pragma unroll
+        for (int ui = 0; ui < 2; ++ui)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int c = dfeat(ui, r, h);
+                const float h0 = fmaxf(z[ui][0][r], 0.0f), h1 = fmaxf(z[ui][1][r], 0.0f);
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    const float av = W2[(32 * u + lo) * kWs + c];
+                    y[u][0] = mfma2(av, h0, y[u][0]);
+                    y[u][1] = mfma2(av, h1, y[u][1]);
+                }
+            }
+#pragma unroll
+        for (int o = 0; o < kOut; ++o) {
+            float s0 = 0.0f, s1 = 0.0f;
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const float wv = W3[o * kHid + dfeat(u, r, h)];
+                    s0 = fmaf(wv, fmaxf(y[u][0][r], 0.0f), s0);
+                    s1 = fmaf(wv, fmaxf(y[u][1][r], 0.0f), s1);
+                }
+            float pa, pb;
+            swap_halves(s0, s1, pa, pb);
+            if (live) out[o * os + i] = 1.0f / (1.0f + expf(-(pa + pb)));
+        }
     }
 }
 
@@ -777,6 +918,23 @@ int make_args(const float* params, const float* pos, int64_t ps, int64_t n, cons
     return FIPT_OK;
 }
 
+int launch_encode(const HgArgs& a, float* ws, int64_t wn, hipStream_t st) {
+    const dim3 grid(grid_points(a.n), kLevels);
+    if (reinterpret_cast<uintptr_t>(a.params) % 16 == 0)
+        hipLaunchKernelGGL(k_hg_encode<true>, grid, dim3(kBlock), 0, st, a, ws, wn);
+    else
+        hipLaunchKernelGGL(k_hg_encode<false>, grid, dim3(kBlock), 0, st, a, ws, wn);
+    return check_hg("hashgrid_encode");
+}
+
+// Workgroups of k_hg_mlp: one per 256 points, up to the three that a CU holds.
+int mlp_blocks(int64_t n) {
+    int dev = 0, cus = 256;
+    if (hipGetDevice(&dev) == hipSuccess)
+        (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+    return (int)std::min<int64_t>(grid_points(n), (int64_t)cus * 3);
+}
+
 // Lanes per slot of a level's table gather: the power of two nearest above
 // a quarter of the mean list length of the level's (light, nonempty) slots,
 // at most 64.
@@ -968,8 +1126,8 @@ int fipt_hashgrid_forward(const float* params, const float* pos, int64_t pos_str
     if (rc) return rc;
     if (!material) return fail(FIPT_EINVAL, "material is NULL");
     if (mat_stride < n) return fail(FIPT_EINVAL, "mat_stride < n");
-    hipLaunchKernelGGL(k_hg_forward<false>, dim3(grid_points(n)), dim3(kBlock), 0, (hipStream_t)stream, a,
-                       material, mat_stride, nullptr, 0);
+    hipLaunchKernelGGL(k_hg_forward, dim3(grid_points(n)), dim3(kBlock), 0, (hipStream_t)stream, a, material,
+                       mat_stride);
     return check_hg("hashgrid_forward");
 }
 
@@ -986,8 +1144,10 @@ int fipt_hashgrid_forward_save(const float* params, const float* pos, int64_t po
     if (workspace_floats < fipt_hashgrid_workspace_floats(n))
         return fail(FIPT_EINVAL, "workspace holds %lld floats, %lld needed", (long long)workspace_floats,
                     (long long)fipt_hashgrid_workspace_floats(n));
-    hipLaunchKernelGGL(k_hg_forward<true>, dim3(grid_points(n)), dim3(kBlock), 0, (hipStream_t)stream, a,
-                       material, mat_stride, workspace, n);
+    rc = launch_encode(a, workspace, n, (hipStream_t)stream);
+    if (rc) return rc;
+    hipLaunchKernelGGL(k_hg_mlp, dim3(mlp_blocks(n)), dim3(kBlock), 0, (hipStream_t)stream, params, workspace, n,
+                       n, material, mat_stride);
     return check_hg("hashgrid_forward_save");
 }
 
