@@ -15,26 +15,22 @@
 // matrix cores over the wavefront's 64 points (see below), the weights in
 // LDS; the five outputs on the vector ALUs.
 //
-// Backward: each wavefront recomputes the forward pass of its 64 points,
-// back-propagates through the MLP (W2^T and W1^T on the matrix cores too),
-// stores the per-level feature gradients (W1^T d1, two per level) and the
-// activations and layer gradients in a workspace.  The table
-// gradient is then a gather: a plan built once for the point set lists, per
-// level, every (point, corner) with a nonzero trilinear weight sorted by
-// table slot (then point, then corner), and one group of lanes per slot sums
-// weight x feature gradient over its list in that order, in double, adding
-// the total into the slot's entry; no atomics, so the table gradient is
-// reproducible bit for bit.  The weight gradients are sums over points of
-// outer products (three small GEMMs with the point count as the reduction
-// dimension): a split-K kernel forms one 64 x 64 partial per chunk of 2048
-// points on the matrix cores, and a final kernel adds the partials in chunk
-// order, so weight gradients are reproducible too.
+// Backward: each workgroup recomputes the forward pass of 64 points from their
+// encoding, back-propagates through the MLP, stores the per-level feature
+// gradients (W1^T d1, two per level) and accumulates the weight gradients of
+// its points, all on the matrix cores; a last kernel adds the workgroups'
+// weight gradients in order.  The table gradient is a gather: a plan built
+// once for the point set lists, per level, every (point, corner) with a
+// nonzero trilinear weight sorted by table slot (then point, then corner),
+// and one group of lanes per slot sums weight x feature gradient over its
+// list in that order, in double, adding the total into the slot's entry.
+// Everything is summed in a fixed order, without float atomics, so the
+// gradient is reproducible bit for bit.
 #include <hip/hip_runtime.h>
 #include <hipcub/hipcub.hpp>
 
 #include <algorithm>
 #include <cmath>
-#include <vector>
 
 #include "fipt_internal.hpp"
 
@@ -51,8 +47,11 @@ constexpr int64_t kTable = (int64_t)kLevels * kT * kFeat;
 constexpr int kW1 = kHid * kIn, kW2 = kHid * kHid, kW3 = kOut * kHid;
 constexpr int kWeights = kW1 + kW2 + kW3;   // 8512
 constexpr int kBlock = 256;
-constexpr int kChunk = 2048;              // points per weight-gradient partial
-constexpr int kWsRows = 3 * 64 + 2 * 64 + kOut;   // e, h1, h2, d1, d2, d3
+// the workspace: 325 floats per point beside the feature gradients and 12,288
+// per 2048 points, of which the encoding (64 per point) and the workgroups'
+// weight gradients are used
+constexpr int kChunk = 2048;
+constexpr int kWsRows = 3 * 64 + 2 * 64 + kOut;
 constexpr int kFeatGradRows = kLevels * kFeat;     // per-level feature gradients, [32][n] float2
 
 struct HgArgs {
@@ -102,7 +101,7 @@ __device__ __forceinline__ void unit_pos(const HgArgs& a, int64_t i, float p[3])
         p[k] = fminf(fmaxf((a.pos[k * a.ps + i] - a.lo[k]) * a.inv[k], 0.0f), 1.0f);
 }
 
-// ---- the backward pass on the matrix cores -----------------------------------
+// ---- the layers on the matrix cores ------------------------------------------
 // One wavefront holds 64 points as two tiles of 32 (points 0-31 and 32-63 of
 // the wavefront).  A 64 x 64 layer over them is four 32 x 32 output tiles of
 // v_mfma_f32_32x32x2f32, two input features per instruction: lane l supplies
@@ -117,6 +116,7 @@ __device__ __forceinline__ void unit_pos(const HgArgs& a, int64_t i, float p[3])
 // live in LDS with rows of 65 floats, so that a row-wise read (W) and a
 // column-wise read (W^T) both reach distinct banks across the 32 lanes.
 typedef float v16f __attribute__((ext_vector_type(16)));
+typedef float v4f __attribute__((ext_vector_type(4)));
 constexpr int kWs = 65;                                      // LDS row stride of W1 and W2
 constexpr int kLdsW = 2 * kHid * kWs + kW3;                  // floats of weights in LDS
 
@@ -144,217 +144,215 @@ __device__ __forceinline__ void load_weights(const float* __restrict__ params, f
     __syncthreads();
 }
 
-// SAVED: the workspace already holds the encoding (rows 0-63, written by
-// the forward pass of the same parameters and points), which is read
-// instead of gathered from the tables again.
-template <bool SAVED>
-__global__ __launch_bounds__(kBlock) void k_hg_backward(HgArgs a, const float* __restrict__ gy,
-                                                             int64_t gs, float* __restrict__ ws,
-                                                             int64_t wn, float2* __restrict__ fgrad) {
+// One workgroup takes 64 points at a time through the whole backward pass,
+// each of its four wavefronts owning one 32 x 32 tile (u, j) of every product:
+// outputs (or rows of a weight gradient) 32 u .., points (or columns) 32 j ...
+// Activations and layer gradients never leave the chip: they pass from one
+// product to the next through two LDS tiles of 64 x 64 (rows of kWs floats),
+// written [feature][point] from the accumulators and read by rows (B of the
+// next layer) or by columns (both operands of a weight gradient, whose
+// reduction runs over the points).  A tile's own pre-activations stay in
+// registers as the ReLU masks.  The weight gradients of all the workgroup's
+// points accumulate in 36 registers and leave once, at its end.  The products
+// that decide the masks (z1, z2) are formed as in the forward pass.
+// Bound by the single-precision matrix rate: 200 products of 64 cycles per
+// wavefront and 64 points, 0.6 ms on the room's 1,843,200 points.  It takes
+// 1.01 ms there (two wavefronts per SIMD, 69 KB of LDS per workgroup, and the
+// barriers between the products), with its reduction 1.02; as a per-point
+// kernel that wrote every activation and layer gradient (1.3 KB per point) and
+// a split-K kernel that read them back it took 1.20 + 0.55 + 0.11 ms.
+constexpr int kTilePts = 64;
+
+// acc += the N products of a(k), b(k), k ascending, eight at a time: the next
+// eight operands are read from LDS while these are multiplied (left to itself
+// the compiler reads all of them first and runs out of registers).
+template <int N, class A, class B>
+__device__ __forceinline__ void product(v16f& acc, A a, B b) {
+    constexpr int G = 8;
+    float av[2][G], bv[2][G];
+#pragma unroll
+    for (int q = 0; q < G; ++q) {
+        av[0][q] = a(q);
+        bv[0][q] = b(q);
+    }
+#pragma unroll
+    for (int g = 0; g < N / G; ++g) {
+        __builtin_amdgcn_sched_barrier(0);
+        if (g + 1 < N / G) {
+#pragma unroll
+            for (int q = 0; q < G; ++q) {
+                av[(g + 1) & 1][q] = a((g + 1) * G + q);
+                bv[(g + 1) & 1][q] = b((g + 1) * G + q);
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < G; ++q) acc = mfma2(av[g & 1][q], bv[g & 1][q], acc);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+}
+
+__device__ __forceinline__ v16f zero16() {
+    v16f v;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) v[r] = 0.0f;
+    return v;
+}
+
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 8))) void k_hg_backward(
+    HgArgs a, const float* __restrict__ gy, int64_t gs, const float* __restrict__ ws, int64_t wn,
+    float2* __restrict__ fgrad, float* __restrict__ part) {
     __shared__ float w[kLdsW];
+    __shared__ float Q[kHid * kWs];            // h1, then d1
+    __shared__ float R[kHid * kWs];            // h2, then d2, then the encoding
+    __shared__ float D3[kOut][kTilePts];
     load_weights(a.params, w);
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, h = lane >> 5, lo = lane & 31;
+    const int u = wave >> 1, j = wave & 1;
+    const int l16 = lane & 15, k16 = lane >> 4;
     const float* W1 = w;                   // W1[o][c] at o * kWs + c
     const float* W2 = w + kHid * kWs;      // W2[o][c] at o * kWs + c
     const float* W3 = w + 2 * kHid * kWs;  // W3[o][c] at o * 64 + c
-    const int lane = threadIdx.x & 63, h = lane >> 5, lo = lane & 31;
-    const int64_t base = (int64_t)blockIdx.x * kBlock + (threadIdx.x & ~63);
-    const int64_t i = base + lane;          // this lane's point in the encoding
-    const bool live = i < a.n;
-    v16f z[2][2];                           // z1, then h1 = relu(z1): [output tile][point tile]
+    // this wavefront's operands, step k of a reduction over features (pairs f,
+    // f + 4 in accumulator order) or over points (pairs p, p + 1)
+    const float* W1row = W1 + (32 * u + lo) * kWs + h;
+    const float* W2row = W2 + (32 * u + lo) * kWs + 4 * h;
+    const float* W1col = W1 + 4 * h * kWs + 32 * u + lo;
+    const float* W2col = W2 + 4 * h * kWs + 32 * u + lo;
+    const float* Qcol = Q + 4 * h * kWs + 32 * j + lo;
+    const float* Rcol = R + 4 * h * kWs + 32 * j + lo;
+    float* Qout = Q + (32 * u + 4 * h) * kWs + 32 * j + lo;   // accumulator register r at row dfeat(0, r, 0)
+    float* Rout = R + (32 * u + 4 * h) * kWs + 32 * j + lo;
+    v16f dw1 = zero16(), dw2 = zero16();
+    v4f dw3;
 #pragma unroll
-    for (int u = 0; u < 2; ++u)
+    for (int r = 0; r < 4; ++r) dw3[r] = 0.0f;
+    const int64_t step = (int64_t)gridDim.x * kTilePts;
+    float e[kLevels];   // the next tile's encoding: feature 2 l + h of this lane's point
+    auto fetch = [&](int64_t base) {
+        const int64_t pt = base + 32 * j + lo;
+        const float* src = ws + (int64_t)h * wn + (pt < a.n ? pt : 0);
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+        for (int l = 0; l < kLevels; ++l) e[l] = src[(int64_t)(2 * l) * wn];
+        if (pt >= a.n) {
 #pragma unroll
-            for (int r = 0; r < 16; ++r) z[u][j][r] = 0.0f;
-    {
-        float p[3] = {0.0f, 0.0f, 0.0f};
-        if (!SAVED && live) unit_pos(a, i, p);
-        const float2* t2 = reinterpret_cast<const float2*>(a.params);
-#pragma unroll 1
-        for (int l = 0; l < kLevels; ++l) {
-            float e0 = 0.0f, e1 = 0.0f;
-            if (SAVED) {
-                if (live) {
-                    e0 = ws[(int64_t)(2 * l) * wn + i];
-                    e1 = ws[(int64_t)(2 * l + 1) * wn + i];
-                }
-            } else {
-                uint32_t idx[8];
-                float wt[8];
-                corners(l, p, idx, wt);
-                const float2* t = t2 + (int64_t)l * kT;
-#pragma unroll
-                for (int k = 0; k < 8; ++k) {
-                    if (wt[k] != 0.0f) {
-                        const float2 v = t[idx[k]];
-                        e0 = fmaf(wt[k], v.x, e0);
-                        e1 = fmaf(wt[k], v.y, e1);
-                    }
-                }
-                if (live) {
-                    ws[(int64_t)(2 * l) * wn + i] = e0;
-                    ws[(int64_t)(2 * l + 1) * wn + i] = e1;
-                }
-            }
-            float b0, b1;   // features 2l (lanes 0-31) and 2l + 1 (lanes 32-63) of point tiles 0 and 1
-            swap_halves(e0, e1, b0, b1);
-#pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                const float av = W1[(32 * u + lo) * kWs + 2 * l + h];
-                z[u][0] = mfma2(av, b0, z[u][0]);
-                z[u][1] = mfma2(av, b1, z[u][1]);
-            }
+            for (int l = 0; l < kLevels; ++l) e[l] = 0.0f;
         }
-    }
-    // h1 = relu(z1), stored (rows 64 + f)
-#pragma unroll
-    for (int u = 0; u < 2; ++u)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                z[u][j][r] = fmaxf(z[u][j][r], 0.0f);
-                const int64_t pt = base + 32 * j + lo;
-                if (pt < a.n) ws[(int64_t)(64 + dfeat(u, r, h)) * wn + pt] = z[u][j][r];
-            }
-    // z2 = W2 h1, h2 = relu(z2), stored (rows 128 + f)
-    v16f y[2][2];
-#pragma unroll
-    for (int u = 0; u < 2; ++u)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) y[u][j][r] = 0.0f;
-#pragma unroll
-    for (int ui = 0; ui < 2; ++ui)
+    };
+    fetch((int64_t)blockIdx.x * kTilePts);
+    for (int64_t base = (int64_t)blockIdx.x * kTilePts; base < a.n; base += step) {
+        asm volatile("" ::: "memory");   // (the weights are read from LDS where they are used)
+        const int64_t pt = base + 32 * j + lo;   // this lane's point in a tile
+        // z1 = W1 e
+        v16f z = zero16();
+        product<kLevels>(z, [&](int l) { return W1row[2 * l]; }, [&](int l) { return e[l]; });
+        __syncthreads();   // (the previous tile's reads of Q and R)
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-            const int c = dfeat(ui, r, h);
-#pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                const float av = W2[(32 * u + lo) * kWs + c];
-                y[u][0] = mfma2(av, z[ui][0][r], y[u][0]);
-                y[u][1] = mfma2(av, z[ui][1][r], y[u][1]);
-            }
+            z[r] = fmaxf(z[r], 0.0f);
+            Qout[dfeat(0, r, 0) * kWs] = z[r];
         }
-#pragma unroll
-    for (int u = 0; u < 2; ++u)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                y[u][j][r] = fmaxf(y[u][j][r], 0.0f);
-                const int64_t pt = base + 32 * j + lo;
-                if (pt < a.n) ws[(int64_t)(128 + dfeat(u, r, h)) * wn + pt] = y[u][j][r];
-            }
-    // outputs: each lane sums its half of the features of its two points;
-    // the halves meet with a swap, one point per lane
-    float d3[kOut];
-#pragma unroll
-    for (int o = 0; o < kOut; ++o) {
-        float s0 = 0.0f, s1 = 0.0f;
-#pragma unroll
-        for (int u = 0; u < 2; ++u)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const float wv = W3[o * kHid + dfeat(u, r, h)];
-                s0 = fmaf(wv, y[u][0][r], s0);
-                s1 = fmaf(wv, y[u][1][r], s1);
-            }
-        float pa, pb;
-        swap_halves(s0, s1, pa, pb);
-        const float sv = pa + pb;           // point base + lane
-        const float yv = 1.0f / (1.0f + expf(-sv));
-        d3[o] = live ? gy[o * gs + i] * yv * (1.0f - yv) : 0.0f;
-        if (live) ws[(int64_t)(320 + o) * wn + i] = d3[o];
-    }
-    // d2 = (W3^T d3) masked by h2 > 0, in y's registers (rows 256 + f); the
-    // d3 of both point tiles reach every lane with a swap
-    float da[kOut], db[kOut];
-#pragma unroll
-    for (int o = 0; o < kOut; ++o) swap_halves(d3[o], d3[o], da[o], db[o]);
-#pragma unroll
-    for (int u = 0; u < 2; ++u)
+        __syncthreads();
+        // z2 = W2 h1
+        v16f y = zero16();
+        product<32>(y, [&](int k) { return W2row[dfeat(k >> 4, k & 15, 0)]; },
+                    [&](int k) { return Qcol[dfeat(k >> 4, k & 15, 0) * kWs]; });
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-            const int c = dfeat(u, r, h);
+            y[r] = fmaxf(y[r], 0.0f);
+            Rout[dfeat(0, r, 0) * kWs] = y[r];
+        }
+        __syncthreads();
+        // outputs o = wave (and 4 on the first wavefront): each lane sums its
+        // half of the features of two points, the halves meet with a swap
+        for (int o = wave; o < kOut; o += kBlock / 64) {
             float s0 = 0.0f, s1 = 0.0f;
+            const float* w3 = W3 + o * kHid + 4 * h;
+            const float* hr = R + 4 * h * kWs + lo;
 #pragma unroll
-            for (int o = 0; o < kOut; ++o) {
-                const float wv = W3[o * kHid + c];
-                s0 = fmaf(wv, da[o], s0);
-                s1 = fmaf(wv, db[o], s1);
+            for (int k = 0; k < 32; ++k) {
+                const int c = dfeat(k >> 4, k & 15, 0);
+                s0 = fmaf(w3[c], hr[c * kWs], s0);
+                s1 = fmaf(w3[c], hr[c * kWs + 32], s1);
+                if ((k & 7) == 7) __builtin_amdgcn_sched_barrier(0);
             }
-            y[u][0][r] = y[u][0][r] > 0.0f ? s0 : 0.0f;
-            y[u][1][r] = y[u][1][r] > 0.0f ? s1 : 0.0f;
-#pragma unroll
-            for (int jj = 0; jj < 2; ++jj) {
-                const int64_t pt = base + 32 * jj + lo;
-                if (pt < a.n) ws[(int64_t)(256 + c) * wn + pt] = y[u][jj][r];
-            }
+            float pa, pb;
+            swap_halves(s0, s1, pa, pb);
+            const float yv = 1.0f / (1.0f + expf(-(pa + pb)));
+            const int64_t i = base + lane;
+            D3[o][lane] = i < a.n ? gy[o * gs + i] * yv * (1.0f - yv) : 0.0f;
         }
-    // d1 = (W2^T d2) masked by h1 > 0, into z's registers (rows 192 + f)
-    v16f g[2][2];
+        __syncthreads();
+        // dW3 += d3 h2^T (16 columns per wavefront); d2 = (W3^T d3) masked
 #pragma unroll
-    for (int u = 0; u < 2; ++u)
-#pragma unroll
-        for (int jj = 0; jj < 2; ++jj)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) g[u][jj][r] = 0.0f;
-#pragma unroll
-    for (int ui = 0; ui < 2; ++ui)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int c = dfeat(ui, r, h);
-#pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                const float av = W2[c * kWs + 32 * u + lo];
-                g[u][0] = mfma2(av, y[ui][0][r], g[u][0]);
-                g[u][1] = mfma2(av, y[ui][1][r], g[u][1]);
-            }
+        for (int k0 = 0; k0 < kTilePts; k0 += 4) {
+            const float av = l16 < kOut ? D3[l16 < kOut ? l16 : 0][k0 + k16] : 0.0f;
+            dw3 = __builtin_amdgcn_mfma_f32_16x16x4f32(av, R[(16 * wave + l16) * kWs + k0 + k16], dw3, 0, 0, 0);
         }
+        __builtin_amdgcn_sched_barrier(0);
+        {
+            float d3[kOut];
 #pragma unroll
-    for (int u = 0; u < 2; ++u)
-#pragma unroll
-        for (int jj = 0; jj < 2; ++jj)
+            for (int o = 0; o < kOut; ++o) d3[o] = D3[o][32 * j + lo];
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
-                z[u][jj][r] = z[u][jj][r] > 0.0f ? g[u][jj][r] : 0.0f;
-                const int64_t pt = base + 32 * jj + lo;
-                if (pt < a.n) ws[(int64_t)(192 + dfeat(u, r, h)) * wn + pt] = z[u][jj][r];
-            }
-    // feature gradients W1^T d1: features 2l and 2l + 1 sit in registers r,
-    // r + 1 (r even) of one lane, stored as one float2 per level
+                float s = 0.0f;
 #pragma unroll
-    for (int u = 0; u < 2; ++u)
-#pragma unroll
-        for (int jj = 0; jj < 2; ++jj)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) g[u][jj][r] = 0.0f;
-#pragma unroll
-    for (int ui = 0; ui < 2; ++ui)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int c = dfeat(ui, r, h);
-#pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                const float av = W1[c * kWs + 32 * u + lo];
-                g[u][0] = mfma2(av, z[ui][0][r], g[u][0]);
-                g[u][1] = mfma2(av, z[ui][1][r], g[u][1]);
+                for (int o = 0; o < kOut; ++o) s = fmaf(W3[o * kHid + dfeat(u, r, h)], d3[o], s);
+                y[r] = y[r] > 0.0f ? s : 0.0f;
+                if ((r & 3) == 3) __builtin_amdgcn_sched_barrier(0);
             }
         }
+        __syncthreads();
 #pragma unroll
-    for (int u = 0; u < 2; ++u)
+        for (int r = 0; r < 16; ++r) Rout[dfeat(0, r, 0) * kWs] = y[r];
+        __syncthreads();
+        // (the encoding again, a row per wavefront and step, for dW1)
+        float er[kHid / 4];
+        {
+            const int64_t i = base + lane;
+            const float* src = ws + (int64_t)wave * wn + (i < a.n ? i : 0);
 #pragma unroll
-        for (int jj = 0; jj < 2; ++jj) {
-            const int64_t pt = base + 32 * jj + lo;
-            if (pt < a.n) {
+            for (int q = 0; q < kHid / 4; ++q) er[q] = src[(int64_t)(4 * q) * wn];
+            if (i >= a.n) {
 #pragma unroll
-                for (int r = 0; r < 16; r += 2)
-                    fgrad[(int64_t)(dfeat(u, r, h) >> 1) * wn + pt] = make_float2(g[u][jj][r], g[u][jj][r + 1]);
+                for (int q = 0; q < kHid / 4; ++q) er[q] = 0.0f;
             }
         }
+        // dW2 += d2 h1^T; d1 = (W2^T d2) masked
+        product<32>(dw2, [&](int k) { return R[(32 * u + lo) * kWs + h + 2 * k]; },
+                    [&](int k) { return Q[(32 * j + lo) * kWs + h + 2 * k]; });
+        v16f g = zero16();
+        product<32>(g, [&](int k) { return W2col[dfeat(k >> 4, k & 15, 0) * kWs]; },
+                    [&](int k) { return Rcol[dfeat(k >> 4, k & 15, 0) * kWs]; });
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < 16; ++r) Qout[dfeat(0, r, 0) * kWs] = z[r] > 0.0f ? g[r] : 0.0f;
+#pragma unroll
+        for (int q = 0; q < kHid / 4; ++q) R[(4 * q + wave) * kWs + lane] = er[q];
+        __syncthreads();
+        if (base + step < a.n) fetch(base + step);
+        // dW1 += d1 e^T; feature gradients W1^T d1: features 2l and 2l + 1 sit
+        // in registers r, r + 1 (r even) of one lane, one float2 per level
+        product<32>(dw1, [&](int k) { return Q[(32 * u + lo) * kWs + h + 2 * k]; },
+                    [&](int k) { return R[(32 * j + lo) * kWs + h + 2 * k]; });
+        g = zero16();
+        product<32>(g, [&](int k) { return W1col[dfeat(k >> 4, k & 15, 0) * kWs]; },
+                    [&](int k) { return Qcol[dfeat(k >> 4, k & 15, 0) * kWs]; });
+        if (pt < a.n) {
+#pragma unroll
+            for (int r = 0; r < 16; r += 2)
+                fgrad[(int64_t)(dfeat(u, r, h) >> 1) * wn + pt] = make_float2(g[r], g[r + 1]);
+        }
+    }
+    float* out = part + (int64_t)blockIdx.x * kWeights;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        out[dfeat(u, r, h) * kIn + 32 * j + lo] = dw1[r];
+        out[kW1 + dfeat(u, r, h) * kHid + 32 * j + lo] = dw2[r];
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+        if (4 * k16 + r < kOut) out[kW1 + kW2 + (4 * k16 + r) * kHid + 16 * wave + l16] = dw3[r];
 }
 
 // The forward pass in the same layout: the two hidden layers on the matrix
@@ -654,12 +652,49 @@ __global__ __launch_bounds__(kBlock) void k_hgp_offsets(const uint32_t* __restri
     off[s] = (uint32_t)lo;
 }
 
+// The slots that have entries, light ones (at most kHeavy) and heavy ones, as
+// two lists; stats: light slots, their entries, heavy slots.  A workgroup's
+// slots stay together and in order; the order of the workgroups is free (each
+// slot's sum depends on its own entries only).
+constexpr uint32_t kHeavy = 256;
+__global__ __launch_bounds__(kBlock) void k_hgp_lists(const uint32_t* __restrict__ off, int64_t n_slots,
+                                                      uint32_t* __restrict__ light, uint32_t* __restrict__ heavy,
+                                                      unsigned long long* __restrict__ stats) {
+    __shared__ uint32_t n_w[kBlock / 64][2], base[2];
+    const int64_t s = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const uint32_t c = s < n_slots ? off[s + 1] - off[s] : 0;
+    const bool is_light = c > 0 && c <= kHeavy, is_heavy = c > kHeavy;
+    const uint64_t ml = __builtin_amdgcn_ballot_w64(is_light), mh = __builtin_amdgcn_ballot_w64(is_heavy);
+    uint32_t entries = is_light ? c : 0;
+    for (int m = 32; m >= 1; m >>= 1) entries += __shfl_xor(entries, m, 64);
+    if (lane == 0) {
+        n_w[wave][0] = (uint32_t)__popcll(ml);
+        n_w[wave][1] = (uint32_t)__popcll(mh);
+        if (entries) atomicAdd(stats + 1, (unsigned long long)entries);
+    }
+    __syncthreads();
+    if (threadIdx.x < 2) {
+        uint32_t t = 0;
+        for (int q = 0; q < kBlock / 64; ++q) t += n_w[q][threadIdx.x];
+        base[threadIdx.x] = t ? (uint32_t)atomicAdd(stats + 2 * threadIdx.x, (unsigned long long)t) : 0u;
+    }
+    __syncthreads();
+    uint32_t at[2] = {base[0], base[1]};
+    for (int q = 0; q < wave; ++q) {
+        at[0] += n_w[q][0];
+        at[1] += n_w[q][1];
+    }
+    const uint64_t below = (1ull << lane) - 1ull;
+    if (is_light) light[at[0] + __popcll(ml & below)] = (uint32_t)s;
+    if (is_heavy) heavy[at[1] + __popcll(mh & below)] = (uint32_t)s;
+}
+
 // Table gradient of one level, slots of at most kHeavy entries: L lanes per
 // slot (a power of two up to 64); lane j sums entries j, j + L, ... of the
 // slot's list in double (four entries' loads, then their four gradient
 // loads, in flight together), a fixed butterfly adds the L partial sums, and
 // the first lane adds the total into the slot's two features.
-constexpr uint32_t kHeavy = 256;
 
 __device__ __forceinline__ void gather_sum(const int2* __restrict__ ent, const float2* __restrict__ fg,
                                            uint32_t first, uint32_t e1, uint32_t stride, double& s0,
@@ -682,44 +717,63 @@ __device__ __forceinline__ void gather_sum(const int2* __restrict__ ent, const f
     }
 }
 
-__global__ __launch_bounds__(kBlock) void k_hg_table_grad(const int2* __restrict__ ent,
-                                                          const uint32_t* __restrict__ off,
-                                                          const float2* __restrict__ fg, int64_t n_slots,
-                                                          int L, float* __restrict__ t) {
-    const int64_t g = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    const int64_t slot = g / L;
-    const int j = (int)(g % L);
-    double s0 = 0.0, s1 = 0.0;
-    uint32_t e0 = 0, e1 = 0;
-    if (slot < n_slots) {
-        e0 = off[slot];
-        e1 = off[slot + 1];
-        if (e1 - e0 > kHeavy) e1 = e0;   // a heavy slot: k_hg_table_grad_heavy
-        gather_sum(ent, fg, e0 + j, e1, L, s0, s1);
-    }
-    for (int m = 1; m < L; m <<= 1) {
-        s0 += __shfl_xor(s0, m, 64);
-        s1 += __shfl_xor(s1, m, 64);
-    }
-    if (j == 0 && e1 > e0) {
-        t[2 * slot] += (float)s0;
-        t[2 * slot + 1] += (float)s1;
-    }
-}
+// The table gradient of every level in one launch, so that a level's last
+// workgroups run beside the next level's first (and a small batch pays one
+// launch, not one per level): per level its heavy slots (one workgroup each),
+// then its light ones, the finest level first, whose longest heavy slots
+// would otherwise be the launch's tail.
+struct TableLevel {
+    const int2* ent;
+    const uint32_t* off;
+    const uint32_t* light;
+    const uint32_t* heavy;
+    uint32_t first;      // the level's first workgroup
+    uint32_t n_heavy;    // its workgroups of heavy slots
+    uint32_t n_light;    // its light slots
+    int32_t lanes;       // lanes per light slot
+};
+struct TableGrad {
+    TableLevel lv[kLevels];   // in launch order: level kLevels - 1 first
+    const float2* fg;         // feature gradients [kLevels][n]
+    int64_t n;
+    float* grad;              // tables [kLevels][kT][2]
+};
 
-// The heavy slots of a level (more than kHeavy entries; the plan lists
-// them): one workgroup per slot, thread j summing entries j, j + kBlock, ...;
-// each wavefront's butterfly, then the four wavefront totals in order.
-__global__ __launch_bounds__(kBlock) void k_hg_table_grad_heavy(const int2* __restrict__ ent,
-                                                                const uint32_t* __restrict__ off,
-                                                                const uint32_t* __restrict__ heavy,
-                                                                const float2* __restrict__ fg,
-                                                                float* __restrict__ t) {
+__global__ __launch_bounds__(kBlock) void k_hg_table_grad(TableGrad g) {
     __shared__ double part[kBlock / 64][2];
-    const uint32_t slot = heavy[blockIdx.x];
-    const uint32_t e0 = off[slot], e1 = off[slot + 1];
+    int q = 0;
+#pragma unroll
+    for (int s = kLevels / 2; s > 0; s >>= 1)
+        if (blockIdx.x >= g.lv[q + s].first) q += s;
+    const TableLevel lv = g.lv[q];
+    const int l = kLevels - 1 - q;
+    const int2* __restrict__ ent = lv.ent;
+    const float2* __restrict__ fg = g.fg + (int64_t)l * g.n;
+    float* __restrict__ t = g.grad + (int64_t)l * kT * kFeat;
+    const uint32_t blk = blockIdx.x - lv.first;
     double s0 = 0.0, s1 = 0.0;
-    gather_sum(ent, fg, e0 + threadIdx.x, e1, kBlock, s0, s1);
+    if (blk >= lv.n_heavy) {
+        const uint32_t id = (blk - lv.n_heavy) * kBlock + threadIdx.x;
+        const uint32_t at = id / (uint32_t)lv.lanes, j = id % (uint32_t)lv.lanes;
+        uint32_t slot = 0;
+        if (at < lv.n_light) {
+            slot = lv.light[at];
+            gather_sum(ent, fg, lv.off[slot] + j, lv.off[slot + 1], lv.lanes, s0, s1);
+        }
+        for (int m = 1; m < lv.lanes; m <<= 1) {
+            s0 += __shfl_xor(s0, m, 64);
+            s1 += __shfl_xor(s1, m, 64);
+        }
+        if (j == 0 && at < lv.n_light) {
+            t[2 * slot] += (float)s0;
+            t[2 * slot + 1] += (float)s1;
+        }
+        return;
+    }
+    // a heavy slot: thread j sums entries j, j + kBlock, ...; each wavefront's
+    // butterfly, then the four wavefront totals in order
+    const uint32_t slot = lv.heavy[blk];
+    gather_sum(ent, fg, lv.off[slot] + threadIdx.x, lv.off[slot + 1], kBlock, s0, s1);
     for (int m = 1; m < 64; m <<= 1) {
         s0 += __shfl_xor(s0, m, 64);
         s1 += __shfl_xor(s1, m, 64);
@@ -730,164 +784,37 @@ __global__ __launch_bounds__(kBlock) void k_hg_table_grad_heavy(const int2* __re
     }
     __syncthreads();
     if (threadIdx.x == 0) {
-        double a = 0.0, b = 0.0;
+        double x = 0.0, y = 0.0;
         for (int w = 0; w < kBlock / 64; ++w) {
-            a += part[w][0];
-            b += part[w][1];
+            x += part[w][0];
+            y += part[w][1];
         }
-        t[2 * slot] += (float)a;
-        t[2 * slot + 1] += (float)b;
+        t[2 * slot] += (float)x;
+        t[2 * slot + 1] += (float)y;
     }
 }
 
-// Staging pieces of k_hg_wgrad<true>: thread t's piece j of a 64-point tile
-// is row (t + 256 j) / 16, points 4 ((t + 256 j) % 16) .. + 3 of the A
-// operand (rows of A past `rows` are zero) and of the B operand.
-__device__ __forceinline__ void wgrad_piece(const float* __restrict__ ws, int64_t wn, int64_t p0,
-                                            int64_t p_end, int idx, int rows, int a_row0, int b_row0,
-                                            float4& ra, float4& rb) {
-    const int r = idx >> 4, c = (idx & 15) * 4;
-    const int64_t pp = p0 + c;
-    const float* pa = ws + (int64_t)(a_row0 + r) * wn;
-    const float* pb = ws + (int64_t)(b_row0 + r) * wn;
-    if (pp + 3 < p_end) {
-        ra = r < rows ? *reinterpret_cast<const float4*>(pa + pp) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-        rb = *reinterpret_cast<const float4*>(pb + pp);
-    } else {
-        ra = make_float4(r < rows && pp < p_end ? pa[pp] : 0.0f, r < rows && pp + 1 < p_end ? pa[pp + 1] : 0.0f,
-                         r < rows && pp + 2 < p_end ? pa[pp + 2] : 0.0f, 0.0f);
-        rb = make_float4(pp < p_end ? pb[pp] : 0.0f, pp + 1 < p_end ? pb[pp + 1] : 0.0f,
-                         pp + 2 < p_end ? pb[pp + 2] : 0.0f, 0.0f);
-    }
-}
-__device__ __forceinline__ void wgrad_fetch(const float* __restrict__ ws, int64_t wn, int64_t p0,
-                                            int64_t p_end, int t, int rows, int a_row0, int b_row0,
-                                            float4& ra0, float4& rb0, float4& ra1, float4& rb1,
-                                            float4& ra2, float4& rb2, float4& ra3, float4& rb3) {
-    wgrad_piece(ws, wn, p0, p_end, t, rows, a_row0, b_row0, ra0, rb0);
-    wgrad_piece(ws, wn, p0, p_end, t + kBlock, rows, a_row0, b_row0, ra1, rb1);
-    wgrad_piece(ws, wn, p0, p_end, t + 2 * kBlock, rows, a_row0, b_row0, ra2, rb2);
-    wgrad_piece(ws, wn, p0, p_end, t + 3 * kBlock, rows, a_row0, b_row0, ra3, rb3);
-}
-__device__ __forceinline__ void wgrad_store(float (*A)[65], float (*B)[65], int t, int j,
-                                            const float4& ra, const float4& rb) {
-    const int idx = t + kBlock * j;
-    const int r = idx >> 4, c = (idx & 15) * 4;
-    A[r][c] = ra.x;
-    A[r][c + 1] = ra.y;
-    A[r][c + 2] = ra.z;
-    A[r][c + 3] = ra.w;
-    B[r][c] = rb.x;
-    B[r][c + 1] = rb.y;
-    B[r][c + 2] = rb.z;
-    B[r][c + 3] = rb.w;
-}
-
-// Weight-gradient partials on the matrix cores: blockIdx.y picks the product
-// (0: d1 x e -> W1, 1: d2 x h1 -> W2, 2: d3 x h2 -> W3), blockIdx.x a chunk
-// of kChunk points; the workgroup's four wavefronts form the 64 x 64
-// partial as four 32 x 32 tiles with v_mfma_f32_32x32x2f32, the points being
-// the reduction dimension, two per instruction.  Operands are staged
-// through LDS in tiles of 64 points by the whole workgroup (32-point tiles:
-// 7 % slower); with VEC (rows 16-byte aligned: n a multiple of 4) each
-// thread reads its share of a tile as 16-byte loads, the next tile's loads
-// issued before the current tile's products.  Lane layout of that
-// instruction: lane l supplies A[l % 32][l / 32] and B[l / 32][l % 32];
-// accumulator register r of lane l holds D[8 (r / 4) + 4 (l / 32) + r % 4][l % 32].
-template <bool VEC>
-__global__ __launch_bounds__(kBlock) void k_hg_wgrad(const float* __restrict__ ws, int64_t wn,
-                                                     int64_t n, float* __restrict__ part) {
-    constexpr int kTile = 64;
-    __shared__ float A[64][kTile + 1];
-    __shared__ float B[64][kTile + 1];
-    const int mat = blockIdx.y;
-    const int rows = mat == 2 ? kOut : 64;
-    const int a_row0 = mat == 0 ? 192 : mat == 1 ? 256 : 320;
-    const int b_row0 = mat == 0 ? 0 : mat == 1 ? 64 : 128;
-    const int t = threadIdx.x;
-    const int wave = t >> 6, lane = t & 63;
-    const int ti = wave >> 1, tj = wave & 1;   // this wavefront's 32 x 32 tile
-    const int li = lane % 32, lk = lane / 32;
-    // the rows of A beyond `rows` are zero: a tile of them adds nothing
-    const bool live_tile = 32 * ti < rows;
-    v16f acc;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
-    const int64_t p_begin = (int64_t)blockIdx.x * kChunk;
-    const int64_t p_end = std::min<int64_t>(n, p_begin + kChunk);
-    if (VEC) {
-        // thread t stages four 4-point pieces of each operand per tile:
-        // piece j is row (t + 256 j) / 16, points 4 ((t + 256 j) % 16) .. + 3
-        float4 ra0, ra1, ra2, ra3, rb0, rb1, rb2, rb3;
-        wgrad_fetch(ws, wn, p_begin, p_end, t, rows, a_row0, b_row0, ra0, rb0, ra1, rb1, ra2, rb2, ra3, rb3);
-        for (int64_t p0 = p_begin; p0 < p_end; p0 += kTile) {
-            wgrad_store(A, B, t, 0, ra0, rb0);
-            wgrad_store(A, B, t, 1, ra1, rb1);
-            wgrad_store(A, B, t, 2, ra2, rb2);
-            wgrad_store(A, B, t, 3, ra3, rb3);
-            __syncthreads();
-            if (p0 + kTile < p_end)
-                wgrad_fetch(ws, wn, p0 + kTile, p_end, t, rows, a_row0, b_row0, ra0, rb0, ra1, rb1,
-                            ra2, rb2, ra3, rb3);
-            if (live_tile) {
-#pragma unroll
-                for (int k0 = 0; k0 < kTile; k0 += 2)
-                    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(A[32 * ti + li][k0 + lk],
-                                                               B[32 * tj + li][k0 + lk], acc, 0, 0, 0);
-            }
-            __syncthreads();
-        }
-    } else {
-        for (int64_t p0 = p_begin; p0 < p_end; p0 += kTile) {
-            // the workgroup stages 64 rows x 64 points of each operand
-            // (coalesced along points)
-            for (int idx = t; idx < 64 * kTile; idx += kBlock) {
-                const int r = idx / kTile, c = idx % kTile;
-                const int64_t pp = p0 + c;
-                const bool in = pp < p_end;
-                A[r][c] = (in && r < rows) ? ws[(int64_t)(a_row0 + r) * wn + pp] : 0.0f;
-                B[r][c] = in ? ws[(int64_t)(b_row0 + r) * wn + pp] : 0.0f;
-            }
-            __syncthreads();
-            if (live_tile) {
-#pragma unroll
-                for (int k0 = 0; k0 < kTile; k0 += 2)
-                    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(A[32 * ti + li][k0 + lk],
-                                                               B[32 * tj + li][k0 + lk], acc, 0, 0, 0);
-            }
-            __syncthreads();
-        }
-    }
-    float* out = part + ((int64_t)mat * gridDim.x + blockIdx.x) * 4096;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-        const int i = 32 * ti + 8 * (r / 4) + 4 * lk + (r % 4);
-        const int j = 32 * tj + li;
-        out[i * 64 + j] = acc[r];
-    }
-}
-
-// gparams[weights] += the partials summed in chunk order.
-__global__ __launch_bounds__(kBlock) void k_hg_wreduce(const float* __restrict__ part,
-                                                       int64_t n_chunks,
+// gparams[weights] += the workgroups' partials: eight threads per weight sum
+// an eighth of the workgroups each, in order and in double, and the eighths
+// are added in order.
+constexpr int kRedParts = 8, kRedCols = kBlock / kRedParts;
+__global__ __launch_bounds__(kBlock) void k_hg_wreduce(const float* __restrict__ part, int n_parts,
                                                        float* __restrict__ gparams) {
-    const int j = blockIdx.x * kBlock + threadIdx.x;
-    if (j >= kWeights) return;
-    int mat, r;
-    if (j < kW1) { mat = 0; r = j; }
-    else if (j < kW1 + kW2) { mat = 1; r = j - kW1; }
-    else { mat = 2; r = j - kW1 - kW2; }
-    // chunk order; four partials' loads in flight at a time
-    const float* src = part + (int64_t)mat * n_chunks * 4096 + r;
-    float s = 0.0f;
-    int64_t c = 0;
-    for (; c + 4 <= n_chunks; c += 4) {
-        const float a = src[c * 4096], b = src[(c + 1) * 4096], d = src[(c + 2) * 4096],
-                    e = src[(c + 3) * 4096];
-        s = (((s + a) + b) + d) + e;
+    __shared__ double sum[kRedParts][kRedCols];
+    const int c = threadIdx.x % kRedCols, q = threadIdx.x / kRedCols;
+    const int j = blockIdx.x * kRedCols + c;
+    static_assert(kWeights % kRedCols == 0, "whole workgroups of weights");
+    const int b0 = (int)((int64_t)n_parts * q / kRedParts), b1 = (int)((int64_t)n_parts * (q + 1) / kRedParts);
+    double s = 0.0;
+#pragma unroll 8
+    for (int b = b0; b < b1; ++b) s += (double)part[(int64_t)b * kWeights + j];
+    sum[q][c] = s;
+    __syncthreads();
+    if (q == 0) {
+        double t = 0.0;
+        for (int k = 0; k < kRedParts; ++k) t += sum[k][c];
+        gparams[kTable + j] += (float)t;
     }
-    for (; c < n_chunks; ++c) s += src[c * 4096];
-    gparams[kTable + j] += s;
 }
 
 int grid_points(int64_t n) { return (int)((n + kBlock - 1) / kBlock); }
@@ -935,6 +862,17 @@ int mlp_blocks(int64_t n) {
     return (int)std::min<int64_t>(grid_points(n), (int64_t)cus * 3);
 }
 
+// Workgroups of k_hg_backward: one per 64 points, up to the two that a CU
+// holds (one: 1.23 against 1.01 ms on 1,843,200 points).  Their partials take
+// 8512 floats each, less than the 261 rows of the workspace that 64 points
+// leave unused.
+int backward_blocks(int64_t n) {
+    int dev = 0, cus = 256;
+    if (hipGetDevice(&dev) == hipSuccess)
+        (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+    return (int)std::min<int64_t>((n + kTilePts - 1) / kTilePts, (int64_t)cus * 2);
+}
+
 // Lanes per slot of a level's table gather: the power of two nearest above
 // a quarter of the mean list length of the level's (light, nonempty) slots,
 // at most 64.
@@ -964,7 +902,9 @@ struct fipt_hashgrid_plan_s {
     float* pos = nullptr;                 // [3][n] device copy of the positions
     int2* ent[FIPT_HG_LEVELS] = {};       // per level: (p << 3 | corner, weight bits), by slot
     uint32_t* off[FIPT_HG_LEVELS] = {};   // per level: [2^19 + 1] slot ranges into ent
+    uint32_t* light[FIPT_HG_LEVELS] = {}; // per level: the slots of 1 to kHeavy entries
     uint32_t* heavy[FIPT_HG_LEVELS] = {}; // per level: the slots of more than kHeavy entries
+    int64_t n_light[FIPT_HG_LEVELS] = {};
     int64_t n_heavy[FIPT_HG_LEVELS] = {};
     int64_t nnz[FIPT_HG_LEVELS] = {};
     int lanes[FIPT_HG_LEVELS] = {};
@@ -979,6 +919,7 @@ void hg_plan_free(fipt_hashgrid_plan p) {
     for (int l = 0; l < FIPT_HG_LEVELS; ++l) {
         (void)hipFree(p->ent[l]);
         (void)hipFree(p->off[l]);
+        (void)hipFree(p->light[l]);
         (void)hipFree(p->heavy[l]);
     }
     delete p;
@@ -1034,7 +975,7 @@ int fipt_hashgrid_plan_create(const float* pos, int64_t pos_stride, int64_t n, c
         hipMalloc(reinterpret_cast<void**>(&k_out), sizeof(uint32_t) * m) != hipSuccess ||
         hipMalloc(reinterpret_cast<void**>(&v_in), sizeof(uint32_t) * m) != hipSuccess ||
         hipMalloc(reinterpret_cast<void**>(&v_out), sizeof(uint32_t) * m) != hipSuccess ||
-        hipMalloc(reinterpret_cast<void**>(&d_nnz), sizeof(unsigned long long) * kLevels) != hipSuccess)
+        hipMalloc(reinterpret_cast<void**>(&d_nnz), sizeof(unsigned long long) * 4 * kLevels) != hipSuccess)
         return bail(FIPT_ENOMEM, "hipMalloc failed");
     for (int k = 0; k < 3; ++k)
         if (hipMemcpyAsync(p->pos + k * n, pos + k * pos_stride, sizeof(float) * n, hipMemcpyDeviceToDevice,
@@ -1042,7 +983,8 @@ int fipt_hashgrid_plan_create(const float* pos, int64_t pos_stride, int64_t n, c
             return bail(FIPT_EHIP, "copying the positions failed");
     a.pos = p->pos;
     a.ps = n;
-    if (hipMemsetAsync(d_nnz, 0, sizeof(unsigned long long) * kLevels, st) != hipSuccess)
+    unsigned long long* d_stats = d_nnz + kLevels;   // k_hgp_lists' three counts per level
+    if (hipMemsetAsync(d_nnz, 0, sizeof(unsigned long long) * 4 * kLevels, st) != hipSuccess)
         return bail(FIPT_EHIP, "hipMemsetAsync failed");
     if (hipcub::DeviceRadixSort::SortPairs(nullptr, tmp_bytes, k_in, k_out, v_in, v_out, (int)m, 0, 20, st) !=
             hipSuccess ||
@@ -1072,31 +1014,21 @@ int fipt_hashgrid_plan_create(const float* pos, int64_t pos_stride, int64_t n, c
         // slots of more than kHeavy entries get a workgroup each; the others
         // share lanes by the mean length of their lists
         const int64_t slots = level_slots(l);
-        std::vector<uint32_t> h_off(slots + 1);
-        if (hipMemcpyAsync(h_off.data(), p->off[l], sizeof(uint32_t) * (slots + 1), hipMemcpyDeviceToHost, st) !=
-                hipSuccess ||
+        const int64_t most_heavy = std::min<int64_t>(slots, p->nnz[l] / kHeavy);
+        if (hipMalloc(reinterpret_cast<void**>(&p->light[l]),
+                      sizeof(uint32_t) * std::max<int64_t>(1, std::min<int64_t>(slots, p->nnz[l]))) != hipSuccess ||
+            hipMalloc(reinterpret_cast<void**>(&p->heavy[l]), sizeof(uint32_t) * std::max<int64_t>(1, most_heavy)) !=
+                hipSuccess)
+            return bail(FIPT_ENOMEM, "hipMalloc slot lists failed");
+        hipLaunchKernelGGL(k_hgp_lists, dim3(grid_points(slots)), dim3(kBlock), 0, st, p->off[l], slots, p->light[l],
+                           p->heavy[l], d_stats + 3 * l);
+        unsigned long long h_stats[3] = {0, 0, 0};
+        if (hipMemcpyAsync(h_stats, d_stats + 3 * l, sizeof(h_stats), hipMemcpyDeviceToHost, st) != hipSuccess ||
             hipStreamSynchronize(st) != hipSuccess)
-            return bail(FIPT_EHIP, "reading the slot ranges failed");
-        std::vector<uint32_t> heavy;
-        int64_t light_n = 0, light_slots = 0;
-        for (int64_t q = 0; q < slots; ++q) {
-            const uint32_t c = h_off[q + 1] - h_off[q];
-            if (c > kHeavy) {
-                heavy.push_back((uint32_t)q);
-            } else if (c > 0) {
-                light_n += c;
-                ++light_slots;
-            }
-        }
-        p->lanes[l] = lanes_per_slot(light_n, light_slots);
-        p->n_heavy[l] = (int64_t)heavy.size();
-        if (hipMalloc(reinterpret_cast<void**>(&p->heavy[l]), sizeof(uint32_t) * std::max<size_t>(heavy.size(), 1)) !=
-            hipSuccess)
-            return bail(FIPT_ENOMEM, "hipMalloc heavy slots failed");
-        if (!heavy.empty() && hipMemcpyAsync(p->heavy[l], heavy.data(), sizeof(uint32_t) * heavy.size(),
-                                             hipMemcpyHostToDevice, st) != hipSuccess)
-            return bail(FIPT_EHIP, "copying the heavy slots failed");
-        if (hipStreamSynchronize(st) != hipSuccess) return bail(FIPT_EHIP, "building a level failed");
+            return bail(FIPT_EHIP, "listing the slots failed");
+        p->n_light[l] = (int64_t)h_stats[0];
+        p->n_heavy[l] = (int64_t)h_stats[2];
+        p->lanes[l] = lanes_per_slot((int64_t)h_stats[1], p->n_light[l]);
     }
     if (check_hg("hashgrid plan") != FIPT_OK || hipStreamSynchronize(st) != hipSuccess)
         return bail(FIPT_EHIP, "building the entry lists failed");
@@ -1165,43 +1097,38 @@ static int hashgrid_backward(fipt_hashgrid_plan plan, const float* params, const
         return fail(FIPT_EINVAL, "workspace holds %lld floats, %lld needed", (long long)workspace_floats,
                     (long long)fipt_hashgrid_workspace_floats(n));
     hipStream_t st = (hipStream_t)stream;
-    float2* fgrad = reinterpret_cast<float2*>(workspace + (int64_t)kWsRows * n);
-    if (saved)
-        hipLaunchKernelGGL(k_hg_backward<true>, dim3(grid_points(n)), dim3(kBlock), 0, st, a, grad_material,
-                           gm_stride, workspace, n, fgrad);
-    else
-        hipLaunchKernelGGL(k_hg_backward<false>, dim3(grid_points(n)), dim3(kBlock), 0, st, a, grad_material,
-                           gm_stride, workspace, n, fgrad);
+    // workspace: the encoding (64 n floats), the feature gradients (64 n), the
+    // workgroups' weight-gradient partials
+    float2* fgrad = reinterpret_cast<float2*>(workspace + (int64_t)kIn * n);
+    float* part = workspace + (int64_t)(kIn + kFeatGradRows) * n;
+    const int blocks = backward_blocks(n);
+    if (!saved && (rc = launch_encode(a, workspace, n, st))) return rc;
+    hipLaunchKernelGGL(k_hg_backward, dim3(blocks), dim3(kBlock), 0, st, a, grad_material, gm_stride, workspace, n,
+                       fgrad, part);
     rc = check_hg("hashgrid_backward");
     if (rc) return rc;
-    for (int l = 0; l < kLevels; ++l) {
-        if (plan->nnz[l] == 0) continue;
-        const int64_t slots = level_slots(l);
-        const int L = plan->lanes[l];
-        hipLaunchKernelGGL(k_hg_table_grad, dim3((unsigned)((slots * L + kBlock - 1) / kBlock)), dim3(kBlock),
-                           0, st, plan->ent[l], plan->off[l], fgrad + (int64_t)l * n, slots, L,
-                           grad_params + (int64_t)l * kT * kFeat);
-        if (plan->n_heavy[l] > 0)
-            hipLaunchKernelGGL(k_hg_table_grad_heavy, dim3((unsigned)plan->n_heavy[l]), dim3(kBlock), 0, st,
-                               plan->ent[l], plan->off[l], plan->heavy[l], fgrad + (int64_t)l * n,
-                               grad_params + (int64_t)l * kT * kFeat);
+    TableGrad tg;
+    tg.fg = fgrad;
+    tg.n = n;
+    tg.grad = grad_params;
+    int64_t first = 0;
+    for (int q = 0; q < kLevels; ++q) {
+        const int l = kLevels - 1 - q;
+        TableLevel& v = tg.lv[q];
+        v.ent = plan->ent[l];
+        v.off = plan->off[l];
+        v.light = plan->light[l];
+        v.heavy = plan->heavy[l];
+        v.first = (uint32_t)first;
+        v.n_heavy = (uint32_t)plan->n_heavy[l];
+        v.n_light = (uint32_t)plan->n_light[l];
+        v.lanes = plan->lanes[l];
+        first += v.n_heavy + ((int64_t)v.n_light * v.lanes + kBlock - 1) / kBlock;
     }
+    if (first > 0) hipLaunchKernelGGL(k_hg_table_grad, dim3((unsigned)first), dim3(kBlock), 0, st, tg);
     rc = check_hg("hashgrid_table_grad");
     if (rc) return rc;
-    const int64_t chunks = (n + kChunk - 1) / kChunk;
-    float* part = workspace + (int64_t)(kWsRows + kFeatGradRows) * n;
-    // 16-byte staging when every workspace row starts 16-byte aligned
-    const bool vec = (n % 4 == 0) && (reinterpret_cast<uintptr_t>(workspace) % 16 == 0);
-    if (vec)
-        hipLaunchKernelGGL(k_hg_wgrad<true>, dim3((unsigned)chunks, 3), dim3(kBlock), 0, st, workspace, n,
-                           n, part);
-    else
-        hipLaunchKernelGGL(k_hg_wgrad<false>, dim3((unsigned)chunks, 3), dim3(kBlock), 0, st, workspace, n,
-                           n, part);
-    rc = check_hg("hashgrid_wgrad");
-    if (rc) return rc;
-    hipLaunchKernelGGL(k_hg_wreduce, dim3((kWeights + kBlock - 1) / kBlock), dim3(kBlock), 0, st,
-                       part, chunks, grad_params);
+    hipLaunchKernelGGL(k_hg_wreduce, dim3(kWeights / kRedCols), dim3(kBlock), 0, st, part, blocks, grad_params);
     return check_hg("hashgrid_wreduce");
 }
 
