@@ -721,19 +721,22 @@ Bvh4Node encode4(const Wide4& w, int e) {
     for (int k = 0; k < 3; ++k) {
         // the stored origin, in units of 2^e (exact: a power-of-two scaling
         // of a normal number); offsets are taken from it as stored
-        n.org[k] = (float)std::ldexp(node_origin(w, k), -e);
-        const double org = (double)n.org[k];
+        const float org_f = (float)std::ldexp(node_origin(w, k), -e);
+        (k == 0 ? n.org_x : k == 1 ? n.org_y : n.org_z) = org_f;
+        const double org = (double)org_f;
         for (int i = 0; i < 4; ++i) {
             if (w.child[i] == kEmptyChild) {
-                n.q[k][i] = 0x7C00;       // +inf
-                n.q[k][4 + i] = 0xFC00;   // -inf
+                n.set_bounds(k, i, 0x7C00, 0xFC00);   // +inf, -inf
                 continue;
             }
-            n.q[k][i] = half_bound_signed(std::ldexp((double)w.lo[k][i], -e) - org, false);
-            n.q[k][4 + i] = half_bound_signed(std::ldexp((double)w.hi[k][i], -e) - org, true);
+            n.set_bounds(k, i, half_bound_signed(std::ldexp((double)w.lo[k][i], -e) - org, false),
+                         half_bound_signed(std::ldexp((double)w.hi[k][i], -e) - org, true));
         }
     }
-    for (int i = 0; i < 4; ++i) n.child[i] = node4_ref(w.child[i]);
+    n.child0 = node4_ref(w.child[0]);
+    n.child1 = node4_ref(w.child[1]);
+    n.child2 = node4_ref(w.child[2]);
+    n.child3 = node4_ref(w.child[3]);
     return n;
 }
 
@@ -800,7 +803,7 @@ int validate4(const fipt::HostBvh& b, const float* verts, const int32_t* tris, i
     const Bvh4Node& en = b.nodes4[idx];
     int used = 0;
     for (int i = 0; i < 4; ++i) {
-        if (en.child[i] != node4_ref(nd.child[i]))
+        if (en.child(i) != node4_ref(nd.child[i]))
             return fail(FIPT_EINVAL, "4-wide node %d: child mismatch", idx);
         if (nd.child[i] != kEmptyChild) {
             ++used;
@@ -808,10 +811,18 @@ int validate4(const fipt::HostBvh& b, const float* verts, const int32_t* tris, i
         }
         // the traversal relies on unused slots holding an inverted box
         for (int k = 0; k < 3; ++k)
-            if (en.q[k][i] != 0x7C00 || en.q[k][4 + i] != 0xFC00)
+            if (en.lo(k, i) != 0x7C00 || en.hi(k, i) != 0xFC00)
                 return fail(FIPT_EINVAL, "4-wide node %d: unused slot %d has a box", idx, i);
     }
     if (used < 1) return fail(FIPT_EINVAL, "4-wide node %d has no children", idx);
+    // the traversal's copies of the planes, one per pair of directions
+    for (int i = 0; i < 4; ++i) {
+        bool same = en.z[1][i] == en.hi(2, i) && en.z[1][4 + i] == en.lo(2, i);
+        for (int s = 0; s < 4; ++s)
+            for (int k = 0; k < 2; ++k)
+                same = same && en.xy[s][4 * k + i] == ((s >> k) & 1 ? en.hi(k, i) : en.lo(k, i));
+        if (!same) return fail(FIPT_EINVAL, "4-wide node %d: slot %d has planes that differ", idx, i);
+    }
     const int here = pushed + used - 1;
     for (int i = 0; i < 4; ++i) {
         const int32_t c = nd.child[i];
@@ -820,8 +831,8 @@ int validate4(const fipt::HostBvh& b, const float* verts, const int32_t* tris, i
         const float hi[3] = {nd.hi[0][i], nd.hi[1][i], nd.hi[2][i]};
         for (int k = 0; k < 3; ++k) {
             auto sv = [](uint16_t h) { return (h & 0x8000u) ? -half_value(h & 0x7FFFu) : half_value(h); };
-            const double dlo = std::ldexp((double)en.org[k] + sv(en.q[k][i]), b.box_exp);
-            const double dhi = std::ldexp((double)en.org[k] + sv(en.q[k][4 + i]), b.box_exp);
+            const double dlo = std::ldexp((double)en.org(k) + sv(en.lo(k, i)), b.box_exp);
+            const double dhi = std::ldexp((double)en.org(k) + sv(en.hi(k, i)), b.box_exp);
             if (!(dlo <= (double)lo[k] && dhi >= (double)hi[k]))
                 return fail(FIPT_EINVAL, "4-wide node %d: encoded slot %d does not enclose its box", idx, i);
         }

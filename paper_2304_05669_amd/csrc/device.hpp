@@ -139,6 +139,8 @@ constexpr float kNoHit = 3.40282347e+38f;
 // product is exact) and the origin times the inverse direction.
 struct RaySlab {
     float ax, ay, az, oxi, oyi, ozi;
+    uint32_t near_xy;   // byte offset of the x and y planes the ray enters by
+    uint32_t near_z;    // and of the z planes, entered ones first
 };
 __device__ __forceinline__ RaySlab ray_slab(V3 o, V3 d, float scale) {
     const float dx = fabsf(d.x) > 1e-20f ? d.x : copysignf(1e-20f, d.x);
@@ -154,17 +156,32 @@ __device__ __forceinline__ RaySlab ray_slab(V3 o, V3 d, float scale) {
     r.oxi = o.x * ix;
     r.oyi = o.y * iy;
     r.ozi = o.z * iz;
+    r.near_xy = (ix < 0.0f ? 16u : 0u) | (iy < 0.0f ? 32u : 0u);
+    r.near_z = iz < 0.0f ? 80u : 64u;
     return r;
 }
 
-__device__ __forceinline__ void order2(float& ka, int32_t& ca, float& kb, int32_t& cb) {
-    const bool s = kb < ka;
-    const float k = s ? kb : ka;
-    kb = s ? ka : kb;
-    ka = k;
-    const int32_t c = s ? cb : ca;
-    cb = s ? ca : cb;
-    ca = c;
+// A child to visit as one 64-bit value: its entry distance (a non-negative
+// float, +inf when missed) in the high word, its reference in the low one.
+// Read as a double such a value is finite and positive, and doubles order as
+// their bits do, so one minimum and one maximum order two children by
+// distance, references and all (single-precision keys with the references
+// selected beside them take five instructions).
+typedef double Child;
+__device__ __forceinline__ Child child_key(float key, int32_t ref) {
+    return __builtin_bit_cast(double, (uint64_t)__float_as_uint(key) << 32 | (uint32_t)ref);
+}
+__device__ __forceinline__ float key_of(Child c) {
+    return __uint_as_float((uint32_t)(__builtin_bit_cast(uint64_t, c) >> 32));
+}
+__device__ __forceinline__ int32_t ref_of(Child c) { return (int32_t)(uint32_t)__builtin_bit_cast(uint64_t, c); }
+__device__ __forceinline__ void order2(Child& a, Child& b) {
+    Child lo, hi;
+    // (the instructions themselves: fmin and fmax canonicalise first)
+    asm("v_min_f64 %0, %1, %2" : "=v"(lo) : "v"(a), "v"(b));
+    asm("v_max_f64 %0, %1, %2" : "=v"(hi) : "v"(a), "v"(b));
+    a = lo;
+    b = hi;
 }
 
 // Load through a pointer known to address global memory.  Scene and point
@@ -234,64 +251,58 @@ __device__ __forceinline__ void stack_pop(int32_t& ref, int32_t*& top, const int
 __device__ __forceinline__ void node4_step(const Bvh4Node* nodes, int32_t& ref, int32_t*& top,
                                            const int32_t* bottom, int stride, const RaySlab& r,
                                            float tmax) {
-    const char* nb = reinterpret_cast<const char*>(nodes) + (uint32_t)ref;
-    const int4 qx = load_global(reinterpret_cast<const int4*>(nb));
-    const int4 qy = load_global(reinterpret_cast<const int4*>(nb + 16));
-    const int4 qz = load_global(reinterpret_cast<const int4*>(nb + 32));
-    const float4 og = load_global(reinterpret_cast<const float4*>(nb + 48));
-    const int4 ch = load_global(reinterpret_cast<const int4*>(nb + 64));
-    int32_t c0 = ch.x, c1 = ch.y, c2 = ch.z, c3 = ch.w;
-    // keep the child load in the same batch as the box loads (otherwise it
-    // is sunk below the miss branch and costs a second memory round trip)
-    asm volatile("" : : "v"(c0), "v"(c1), "v"(c2), "v"(c3));
+    const char* nb = reinterpret_cast<const char*>(nodes);
+    const uint32_t at = (uint32_t)ref | r.near_xy;
+    const int4 qn = load_global(reinterpret_cast<const int4*>(nb + at));            // near x, y
+    const int4 qf = load_global(reinterpret_cast<const int4*>(nb + (at ^ 48u)));    // far x, y
+    const int4 qz = load_global(reinterpret_cast<const int4*>(nb + ((uint32_t)ref | r.near_z)));
+    const int4 ga = load_global(reinterpret_cast<const int4*>(nb + (uint32_t)ref + 96));
+    const int4 gb = load_global(reinterpret_cast<const int4*>(nb + (uint32_t)ref + 112));
+    // keep the five loads in one batch (otherwise some are issued only after
+    // the first have arrived: a second memory round trip)
+    asm volatile("" : : "v"(qn.x), "v"(qf.x), "v"(qz.x), "v"(ga.x), "v"(gb.x));
     // per axis: distance at the node origin
     const float ax = r.ax, ay = r.ay, az = r.az;
-    const float bx = fmaf(og.x, ax, -r.oxi);
-    const float by = fmaf(og.y, ay, -r.oyi);
-    const float bz = fmaf(og.z, az, -r.ozi);
-    // near planes are the low bounds for a positive direction component,
-    // else the high bounds: words (lo0|lo1, lo2|lo3, hi0|hi1, hi2|hi3)
-    const bool sx = ax < 0.0f, sy = ay < 0.0f, sz = az < 0.0f;
-    const uint32_t nx01 = sx ? qx.z : qx.x, nx23 = sx ? qx.w : qx.y;
-    const uint32_t fx01 = sx ? qx.x : qx.z, fx23 = sx ? qx.y : qx.w;
-    const uint32_t ny01 = sy ? qy.z : qy.x, ny23 = sy ? qy.w : qy.y;
-    const uint32_t fy01 = sy ? qy.x : qy.z, fy23 = sy ? qy.y : qy.w;
-    const uint32_t nz01 = sz ? qz.z : qz.x, nz23 = sz ? qz.w : qz.y;
-    const uint32_t fz01 = sz ? qz.x : qz.z, fz23 = sz ? qz.y : qz.w;
-    float k0 = box_entry(half_lo(nx01), half_lo(fx01), half_lo(ny01), half_lo(fy01), half_lo(nz01),
-                         half_lo(fz01), ax, bx, ay, by, az, bz);
-    float k1 = box_entry(half_hi(nx01), half_hi(fx01), half_hi(ny01), half_hi(fy01), half_hi(nz01),
-                         half_hi(fz01), ax, bx, ay, by, az, bz);
-    float k2 = box_entry(half_lo(nx23), half_lo(fx23), half_lo(ny23), half_lo(fy23), half_lo(nz23),
-                         half_lo(fz23), ax, bx, ay, by, az, bz);
-    float k3 = box_entry(half_hi(nx23), half_hi(fx23), half_hi(ny23), half_hi(fy23), half_hi(nz23),
-                         half_hi(fz23), ax, bx, ay, by, az, bz);
-    // sorting network on four keys; a missed child keeps key +inf and one
-    // entered beyond the current hit a key above tmax (finite: kNoHit
-    // before the first hit), so both sort after every child to visit, and
-    // the sorted keys compared with tmax say which children to visit
-    order2(k0, c0, k1, c1);
-    order2(k2, c2, k3, c3);
-    order2(k0, c0, k2, c2);
-    order2(k1, c1, k3, c3);
-    order2(k1, c1, k2, c2);
-    if (!(k0 <= tmax)) {
+    const float bx = fmaf(__int_as_float(ga.y), ax, -r.oxi);
+    const float by = fmaf(__int_as_float(ga.w), ay, -r.oyi);
+    const float bz = fmaf(__int_as_float(gb.y), az, -r.ozi);
+    // words (slots 0 and 1, slots 2 and 3)
+    const uint32_t nx01 = qn.x, nx23 = qn.y, ny01 = qn.z, ny23 = qn.w, nz01 = qz.x, nz23 = qz.y;
+    const uint32_t fx01 = qf.x, fx23 = qf.y, fy01 = qf.z, fy23 = qf.w, fz01 = qz.z, fz23 = qz.w;
+    Child c0 = child_key(box_entry(half_lo(nx01), half_lo(fx01), half_lo(ny01), half_lo(fy01), half_lo(nz01),
+                                   half_lo(fz01), ax, bx, ay, by, az, bz), gb.x);
+    Child c1 = child_key(box_entry(half_hi(nx01), half_hi(fx01), half_hi(ny01), half_hi(fy01), half_hi(nz01),
+                                   half_hi(fz01), ax, bx, ay, by, az, bz), gb.z);
+    Child c2 = child_key(box_entry(half_lo(nx23), half_lo(fx23), half_lo(ny23), half_lo(fy23), half_lo(nz23),
+                                   half_lo(fz23), ax, bx, ay, by, az, bz), ga.x);
+    Child c3 = child_key(box_entry(half_hi(nx23), half_hi(fx23), half_hi(ny23), half_hi(fy23), half_hi(nz23),
+                                   half_hi(fz23), ax, bx, ay, by, az, bz), ga.z);
+    // sorting network on the four; a missed child keeps key +inf and one
+    // entered beyond the current hit a key above tmax (finite: kNoHit before
+    // the first hit), so both sort after every child to visit, and the sorted
+    // keys compared with tmax say which children to visit
+    order2(c0, c1);
+    order2(c2, c3);
+    order2(c0, c2);
+    order2(c1, c3);
+    order2(c1, c2);
+    if (!(key_of(c0) <= tmax)) {
         stack_pop(ref, top, bottom, stride);
         return;
     }
-    if (k3 <= tmax) {
-        *top = c3;
+    if (key_of(c3) <= tmax) {
+        *top = ref_of(c3);
         top += stride;
     }
-    if (k2 <= tmax) {
-        *top = c2;
+    if (key_of(c2) <= tmax) {
+        *top = ref_of(c2);
         top += stride;
     }
-    if (k1 <= tmax) {
-        *top = c1;
+    if (key_of(c1) <= tmax) {
+        *top = ref_of(c1);
         top += stride;
     }
-    ref = c0;
+    ref = ref_of(c0);
 }
 
 // ---- the chain of boxes around a point ------------------------------------
@@ -308,15 +319,25 @@ constexpr int kChainMax = 16;   // levels kept (one per lane of the first 16)
 
 // Node data through the constant address space: with a wave-uniform node
 // the compiler reads it with scalar loads into scalar registers.
-typedef const __attribute__((address_space(4))) int4* cint4p;
-typedef const __attribute__((address_space(4))) float4* cfloat4p;
 __device__ __forceinline__ int4 load_uniform(const void* p) {
     const gint4 v = *(const __attribute__((address_space(4))) gint4*)p;
     return make_int4(v.x, v.y, v.z, v.w);
 }
-__device__ __forceinline__ float4 load_uniform_f(const void* p) {
-    const gfloat4 v = *(const __attribute__((address_space(4))) gfloat4*)p;
-    return make_float4(v.x, v.y, v.z, v.w);
+struct UniformNode {
+    int4 qx, qy, qz;   // per axis: low words of slots 0 1 and 2 3, high words
+    V3 og;
+    int4 ch;
+};
+__device__ __forceinline__ UniformNode uniform_node(const char* nb) {
+    const int4 lo = load_uniform(nb), hi = load_uniform(nb + 48), z = load_uniform(nb + 64),
+               ga = load_uniform(nb + 96), gb = load_uniform(nb + 112);
+    UniformNode u;
+    u.qx = make_int4(lo.x, lo.y, hi.x, hi.y);
+    u.qy = make_int4(lo.z, lo.w, hi.z, hi.w);
+    u.qz = z;
+    u.og = v3(__int_as_float(ga.y), __int_as_float(ga.w), __int_as_float(gb.y));
+    u.ch = make_int4(gb.x, gb.z, ga.x, ga.z);
+    return u;
 }
 
 // Half j of the four packed in a (lo01, lo23) or (hi01, hi23) word pair.
@@ -341,9 +362,9 @@ __device__ __forceinline__ int point_chain(const Bvh4Node* nodes, float scale, V
     chain = 0;
     while (L < kChainMax) {
         const char* nb = reinterpret_cast<const char*>(nodes) + (uint32_t)node;
-        const int4 qx = load_uniform(nb), qy = load_uniform(nb + 16), qz = load_uniform(nb + 32);
-        const float4 og = load_uniform_f(nb + 48);
-        const int4 ch = load_uniform(nb + 64);
+        const UniformNode u = uniform_node(nb);
+        const int4 &qx = u.qx, &qy = u.qy, &qz = u.qz, &ch = u.ch;
+        const V3 og = u.og;
         int slot = -1;
 #pragma unroll
         for (int j = 3; j >= 0; --j) {
@@ -396,24 +417,23 @@ template <int A, int B, int C>
 __device__ __forceinline__ void chain_siblings3(const int4& qx, const int4& qy, const int4& qz,
                                                 const int4& ch, const RaySlab& r, float bx,
                                                 float by, float bz, int32_t*& top, int stride) {
-    float ka = chain_key<A>(qx, qy, qz, r, bx, by, bz);
-    float kb = chain_key<B>(qx, qy, qz, r, bx, by, bz);
-    float kc = chain_key<C>(qx, qy, qz, r, bx, by, bz);
     const int32_t refs[4] = {ch.x, ch.y, ch.z, ch.w};
-    int32_t ca = refs[A], cb = refs[B], cc = refs[C];
-    order2(ka, ca, kb, cb);
-    order2(kb, cb, kc, cc);
-    order2(ka, ca, kb, cb);
-    if (kc < INFINITY) {
-        *top = cc;
+    Child ca = child_key(chain_key<A>(qx, qy, qz, r, bx, by, bz), refs[A]);
+    Child cb = child_key(chain_key<B>(qx, qy, qz, r, bx, by, bz), refs[B]);
+    Child cc = child_key(chain_key<C>(qx, qy, qz, r, bx, by, bz), refs[C]);
+    order2(ca, cb);
+    order2(cb, cc);
+    order2(ca, cb);
+    if (key_of(cc) < INFINITY) {
+        *top = ref_of(cc);
         top += stride;
     }
-    if (kb < INFINITY) {
-        *top = cb;
+    if (key_of(cb) < INFINITY) {
+        *top = ref_of(cb);
         top += stride;
     }
-    if (ka < INFINITY) {
-        *top = ca;
+    if (key_of(ca) < INFINITY) {
+        *top = ref_of(ca);
         top += stride;
     }
 }
@@ -425,9 +445,9 @@ __device__ __forceinline__ void chain_siblings3(const int4& qx, const int4& qy, 
 __device__ __forceinline__ void chain_step(const Bvh4Node* nodes, int32_t node, int skip,
                                            const RaySlab& r, int32_t*& top, int stride) {
     const char* nb = reinterpret_cast<const char*>(nodes) + (uint32_t)node;
-    const int4 qx = load_uniform(nb), qy = load_uniform(nb + 16), qz = load_uniform(nb + 32);
-    const float4 og = load_uniform_f(nb + 48);
-    const int4 ch = load_uniform(nb + 64);
+    const UniformNode u = uniform_node(nb);
+    const int4 &qx = u.qx, &qy = u.qy, &qz = u.qz, &ch = u.ch;
+    const V3 og = u.og;
     const float bx = fmaf(og.x, r.ax, -r.oxi);
     const float by = fmaf(og.y, r.ay, -r.oyi);
     const float bz = fmaf(og.z, r.az, -r.ozi);

@@ -72,24 +72,50 @@ struct Wide4 {
     int32_t child[4];
 };
 
-// The device form of a 4-wide node, 128 bytes of which the traversal reads
-// the first 80 in five 16-byte loads.  Bounds are in units of 2^E, one
-// exponent E for the whole tree (HostBvh::box_exp).  Per axis, q[axis]
-// holds the slots' low bounds then high bounds as signed half-precision
-// offsets from org[axis]:  bound = (org + offset) 2^E.  The origin is the
+// The device form of a 4-wide node, one 128-byte line, of which a traversal
+// step reads five 16-byte pieces.  Bounds are in units of 2^E, one exponent E
+// for the whole tree (HostBvh::box_exp): per axis signed half-precision
+// offsets from the node origin, bound = (org + offset) 2^E.  The origin is the
 // low bound of the slot thinnest on that axis, so a flat box (a wall, a
-// floor) keeps its thickness and a ray leaving such a surface does not
-// start inside it; other bounds carry the half-precision error of their
-// distance from the origin.  Offsets are rounded outward (lows down, highs
-// up), so every decoded box contains the single-precision box it encodes;
-// an unused slot has low +inf and high -inf, which no ray enters.
+// floor) keeps its thickness and a ray leaving such a surface does not start
+// inside it; other bounds carry the half-precision error of their distance
+// from the origin.  Offsets are rounded outward (lows down, highs up), so
+// every decoded box contains the single-precision box it encodes; an unused
+// slot has low +inf and high -inf, which no ray enters.
+// A ray enters a box through its low plane on an axis when it goes up that
+// axis, else through its high plane; so that it need not select them, the x
+// and y planes are held once for each pair of directions (piece s: the planes
+// entered by a ray going down x if s & 1 and down y if s & 2; the planes it
+// leaves by are piece 3 - s) and the z planes in both orders.  The child
+// references and the origin share two pieces such that each reference has a
+// free word after it (see node4_step).
 struct alignas(16) Bvh4Node {
-    uint16_t q[3][8];    // bytes 0..47: x, y, z; each lo[0..3], hi[0..3]
-    float org[3];        // bytes 48..59
-    int32_t spare;       // bytes 60..63
-    int32_t child[4];    // bytes 64..79: an inner child as the byte offset of its
-                         // node (index x 128), a leaf as in the binary tree
-    int32_t pad[12];
+    uint16_t xy[4][8];   // bytes 0..63: x planes of the four slots, y planes
+    uint16_t z[2][8];    // bytes 64..95: lows and highs, highs and lows
+    int32_t child2;      // bytes 96..111
+    float org_x;
+    int32_t child3;
+    float org_y;
+    int32_t child0;      // bytes 112..127: an inner child as the byte offset of
+    float org_z;         // its node (index x 128), a leaf as in the binary tree
+    int32_t child1;
+    int32_t spare;
+
+    // half-precision low / high offset of a slot on an axis
+    uint16_t lo(int axis, int slot) const { return axis == 2 ? z[0][slot] : xy[0][4 * axis + slot]; }
+    uint16_t hi(int axis, int slot) const { return axis == 2 ? z[0][4 + slot] : xy[3][4 * axis + slot]; }
+    float org(int axis) const { return axis == 0 ? org_x : axis == 1 ? org_y : org_z; }
+    int32_t child(int slot) const {
+        return slot == 0 ? child0 : slot == 1 ? child1 : slot == 2 ? child2 : child3;
+    }
+    void set_bounds(int axis, int slot, uint16_t low, uint16_t high) {
+        if (axis == 2) {
+            z[0][slot] = z[1][4 + slot] = low;
+            z[0][4 + slot] = z[1][slot] = high;
+            return;
+        }
+        for (int s = 0; s < 4; ++s) xy[s][4 * axis + slot] = (s >> axis) & 1 ? high : low;
+    }
 };
 static_assert(sizeof(Bvh4Node) == 128, "4-wide node is one 128-byte line");
 // node byte offsets stay below 2^31: an inner reference is a non-negative
