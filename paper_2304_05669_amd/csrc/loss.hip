@@ -42,10 +42,61 @@ struct SigmaTable {
 
 // Tone maps in double: the per-point arithmetic of this kernel runs in
 // float64, which removes the float32 cancellation in Lr - Lgt that would
-// otherwise dominate the gradient of well-fit points.  The log-sRGB map
-// Gamma(x) = sRGB-OETF(log(1 + x)) and its derivative share one log1p and
-// one power, the power taken as exp(log(u) / 2.4) (a few ulp in double,
-// and several times cheaper than a general pow).
+// otherwise dominate the gradient of well-fit points.
+//
+// The log-sRGB map Gamma(x) = sRGB-OETF(log(1 + x)) binds these kernels to the
+// vector ALUs, six logarithms, six powers and three quotients per point.  The
+// library's log1p, log, exp and division take about 150 instructions a map;
+// the forms here take about 60, to the same few units in the last place,
+// because the reciprocals and the power start from the hardware's
+// approximations and need one step of high order: the masked loss of 600,001
+// points 44 -> 23 us, the fused grid loss of 1,843,200 points 150 -> 111 us
+// (99 without a tone map: what is left is the planes' memory traffic).
+
+// 1 / v: the hardware reciprocal (relative error d of about 2^-23) and one
+// step of third order (error d^3).
+__device__ __forceinline__ double rcp_f64(double v) {
+    const double r = __builtin_amdgcn_rcp(v);
+    const double e = fma(-v, r, 1.0);
+    return fma(r, fma(e, e, e), r);
+}
+
+// log(1 + x) for finite x > 0, v = 1 + x as rounded.  With v = 2^e m, m in
+// [1/sqrt 2, sqrt 2): log v = e log 2 + 2 atanh(s), s = f / (2 + f), f = m - 1
+// with v's rounding error put back (f = x where e = 0, so small x keep their
+// precision); atanh from its polynomial in s^2 (interpolated at the seven
+// Chebyshev points of the range: error below 5e-18 of 2 s).
+__device__ __forceinline__ double log1p_f64(double x, double v) {
+    double m = __builtin_amdgcn_frexp_mant(v);
+    int e = __builtin_amdgcn_frexp_exp(v);
+    const bool low = m < 0.70710678118654752;
+    m = low ? 2.0 * m : m;
+    e = low ? e - 1 : e;
+    const double f = (m - 1.0) + __builtin_amdgcn_ldexp(x - (v - 1.0), -e);
+    const double s = f * rcp_f64(2.0 + f);
+    const double z = s * s;
+    double p = 0.14616484198366603;
+    p = fma(p, z, 0.1533171880828007);
+    p = fma(p, z, 0.18182889209266595);
+    p = fma(p, z, 0.22222211133642084);
+    p = fma(p, z, 0.2857142862598255);
+    p = fma(p, z, 0.3999999999989949);
+    p = fma(p, z, 0.666666666666667);
+    // log 2 as a part of 21 bits (its multiples are exact) and the rest
+    const double k = (double)e;
+    return fma(k, 0.6931467056274414, 2.0 * s) + fma(k, 4.7493250390316726e-07, s * z * p);
+}
+
+// u^(-7/12) = u^(5/12) / u: z, the single-precision u^(-1/12), gives
+// t = u z^12 = 1 + eps with |eps| below 1e-5, and u^(-7/12) = z^7 t^(-7/12)
+// by three terms of the binomial series (error 0.4 eps^3).
+__device__ __forceinline__ double pow_m7_12(double u) {
+    const double z = (double)__builtin_amdgcn_exp2f(__builtin_amdgcn_logf((float)u) * (-1.0f / 12.0f));
+    const double z2 = z * z, z3 = z2 * z, z6 = z3 * z3;
+    const double eps = fma(u * z6, z6, -1.0);
+    return (z6 * z) * fma(eps, fma(eps, 133.0 / 288.0, -7.0 / 12.0), 1.0);
+}
+
 template <int TONE>
 __device__ __forceinline__ double tone_vd(double x, double& d) {
     if (TONE == 0) {
@@ -56,14 +107,12 @@ __device__ __forceinline__ double tone_vd(double x, double& d) {
         d = 0.0;
         return 0.0;
     }
-    const double u = log1p(x);
-    if (u <= 0.0031308) {
-        d = 12.92 / (1.0 + x);
-        return 12.92 * u;
-    }
-    const double p = exp(log(u) * (1.0 / 2.4));
-    d = (1.055 / 2.4) * p / (u * (1.0 + x));
-    return 1.055 * p - 0.055;
+    const double v = 1.0 + x;
+    const double u = log1p_f64(x, v), r = rcp_f64(v), q = pow_m7_12(u);
+    const bool linear = u <= 0.0031308;
+    d = (linear ? 12.92 : (1.055 / 2.4) * q) * r;
+    const double y = linear ? 12.92 * u : fma(1.055, u * q, -0.055);
+    return x < INFINITY ? y : x;   // (the derivative at infinity is NaN)
 }
 template <int TONE>
 __device__ __forceinline__ double tone(double x) {
@@ -378,7 +427,7 @@ __device__ __forceinline__ void grid_render_loss(const GridPlanDev& P, const flo
 }
 
 // Without the tone map the kernel fits 96 registers (5 wavefronts per SIMD,
-// no spills); the log-sRGB form keeps the compiler's allocation.
+// two spilled), the log-sRGB form 128 (4).
 #define FIPT_GRID_LOSS_ARGS                                                                    \
     GridPlanDev P, const float* __restrict__ grid, GridFrame gf, const float* __restrict__ sh, \
         int64_t ss, int K, const float* __restrict__ obs, int64_t os, SigmaTable tab,          \
@@ -389,7 +438,8 @@ k_grid_render_loss(FIPT_GRID_LOSS_ARGS) {
     grid_render_loss<0, GP>(P, grid, gf, sh, ss, K, obs, os, tab, partials, gq, gqs);
 }
 template <bool GP>
-__global__ __launch_bounds__(kBlock) void k_grid_render_loss_log(FIPT_GRID_LOSS_ARGS) {
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 8))) void
+k_grid_render_loss_log(FIPT_GRID_LOSS_ARGS) {
     grid_render_loss<1, GP>(P, grid, gf, sh, ss, K, obs, os, tab, partials, gq, gqs);
 }
 
