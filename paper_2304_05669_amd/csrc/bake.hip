@@ -43,7 +43,7 @@ constexpr int kGridWavesPerCu = 20;
 // Bake point p of job b with the calling wavefront.
 template <bool COUNT, bool VOXEL>
 __device__ __forceinline__ void bake_point(const BakeLaunch& b, const float* sigma, int64_t p, int lane,
-                                           int32_t* stack, uint32_t& n_rays, uint32_t& n_nodes,
+                                           uint32_t stack, uint32_t& n_rays, uint32_t& n_nodes,
                                            uint32_t& n_tris, uint32_t& n_hits) {
     const int K = b.K;
     const int P = 3 + 6 * K;
@@ -121,7 +121,7 @@ __device__ __forceinline__ void bake_point(const BakeLaunch& b, const float* sig
         h.u = h.v = 0.0f;
         if (shoot) {
             if (COUNT) ++n_rays;
-            h = dev::trace<COUNT>(b.sc, o, wi, stack, kBlock, n_nodes, n_tris);
+            h = dev::trace<COUNT>(b.sc, o, wi, stack, n_nodes, n_tris);
             if (COUNT && h.leaf >= 0) ++n_hits;
             const V3 R = VOXEL ? dev::radiance_voxel(b.sc, h, o, wi) : dev::radiance(b.sc, h);
             if (lobe == 0) {
@@ -200,7 +200,7 @@ __device__ __forceinline__ bool is_leaf(int32_t ref) {
 template <bool COUNT, bool VOXEL>
 __device__ __forceinline__ void bake_point_refill(const BakeLaunch& b, const float* sigma, int64_t p,
                                                   int lane,
-                                                  int32_t* stack, uint32_t& n_rays,
+                                                  uint32_t stack, uint32_t& n_rays,
                                                   uint32_t& n_nodes, uint32_t& n_tris,
                                                   uint32_t& n_hits, uint32_t& n_node_steps,
                                                   uint32_t& n_tri_steps, uint32_t& n_chain) {
@@ -270,7 +270,7 @@ __device__ __forceinline__ void bake_point_refill(const BakeLaunch& b, const flo
     V3 d = v3(0.0f, 0.0f, 1.0f);
     dev::RaySlab rs = dev::ray_slab(o, d, sc.box_scale);
     int32_t ref = kDone;
-    int32_t* top = stack;
+    uint32_t top = stack;
     dev::Hit h;
     h.leaf = -1;
     h.t = dev::kNoHit;
@@ -352,6 +352,7 @@ __device__ __forceinline__ void bake_point_refill(const BakeLaunch& b, const flo
                         }
                         if (shoot) {
                             if (COUNT) ++n_rays;
+                            d = sc.ray_unit * d;
                             rs = dev::ray_slab(o, d, sc.box_scale);
                             // start below the point's chain: its siblings
                             // the ray hits are pushed level by level
@@ -359,7 +360,7 @@ __device__ __forceinline__ void bake_point_refill(const BakeLaunch& b, const flo
                             for (int i = 0; i < chain_len; ++i) {
                                 const int32_t cw = __builtin_amdgcn_readlane(chain, i);
                                 if (COUNT) ++n_chain;
-                                dev::chain_step(sc.nodes, cw & ~3, cw & 3, rs, top, kBlock);
+                                dev::chain_step(sc.nodes, cw & ~3, cw & 3, rs, top);
                             }
                             ref = chain_end;
                             h.leaf = -1;
@@ -389,7 +390,7 @@ __device__ __forceinline__ void bake_point_refill(const BakeLaunch& b, const flo
             const uint64_t unparked = dev::ballot(waits) & ~dev::ballot(leaf);
             if (waits && leaf) {
                 pend = ref;
-                dev::stack_pop(ref, top, stack, kBlock);
+                dev::stack_pop(ref, top, stack);
             }
             const bool inner = ref >= 0;
             // Stop descending once fewer than kSearchMin lanes are still
@@ -404,7 +405,7 @@ __device__ __forceinline__ void bake_point_refill(const BakeLaunch& b, const flo
             if (COUNT && lane == 0) ++n_node_steps;
             if (inner) {
                 if (COUNT) ++n_nodes;
-                dev::node4_step(sc.nodes, ref, top, stack, kBlock, rs, h.t);
+                dev::node4_step(sc.nodes, ref, top, stack, rs, h.t);
             }
         }
         // ---- leaves ---------------------------------------------------------
@@ -437,7 +438,7 @@ __global__ __launch_bounds__(kBlock) FIPT_BAKE_OCCUPANCY void k_bake(BakeLaunch 
                                                                      uint64_t* stats) {
     __shared__ int32_t s_stack[kStackSize * kBlock];
     const int lane = threadIdx.x & 63;
-    int32_t* stack = s_stack + threadIdx.x;
+    const uint32_t stack = dev::lds_address(s_stack + threadIdx.x);
     uint32_t n_rays = 0, n_nodes = 0, n_tris = 0, n_hits = 0, n_node_steps = 0, n_tri_steps = 0,
              n_chain = 0;
     uint32_t queue = point_queue(b.n, lane);
@@ -472,6 +473,7 @@ __device__ __forceinline__ BakeLaunch uniform_job(const BakeLaunch& j) {
     b.sc.rad = static_cast<const TriRad*>(up(j.sc.rad));
     b.sc.n_tris = wave_uniform(j.sc.n_tris);
     b.sc.box_scale = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(j.sc.box_scale)));
+    b.sc.ray_unit = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(j.sc.ray_unit)));
     b.sc.vox = nullptr;   // serving scenes have no voxel cache
     b.sc.vox_res = 0;
     b.pts = static_cast<const float*>(up(j.pts));
@@ -498,7 +500,7 @@ __global__ __launch_bounds__(kBlock) FIPT_BAKE_OCCUPANCY void k_bake_tiles(const
                                                                            int32_t* counters) {
     __shared__ int32_t s_stack[kStackSize * kBlock];
     const int lane = threadIdx.x & 63;
-    int32_t* stack = s_stack + threadIdx.x;
+    const uint32_t stack = dev::lds_address(s_stack + threadIdx.x);
     uint32_t a = 0, bb = 0, c = 0, d = 0, e = 0, f = 0, g = 0;   // counters, unused here
     const int64_t total = tiles[n_tiles - 1].first + tiles[n_tiles - 1].job.n;
     uint32_t queue = point_queue(total, lane);
@@ -530,7 +532,7 @@ __global__ __launch_bounds__(kBlock) void k_cast_rays(DeviceScene sc, const floa
     const V3 o = v3(rays[i], rays[stride + i], rays[2 * stride + i]);
     const V3 d = v3(rays[3 * stride + i], rays[4 * stride + i], rays[5 * stride + i]);
     uint32_t z0 = 0, z1 = 0;
-    const dev::Hit h = dev::trace<false>(sc, o, d, s_stack + threadIdx.x, kBlock, z0, z1);
+    const dev::Hit h = dev::trace<false>(sc, o, d, dev::lds_address(s_stack + threadIdx.x), z0, z1);
     hit_tri[i] = h.leaf >= 0 ? sc.tris[h.leaf].orig : -1;
     if (hit_tuv) {
         hit_tuv[i] = h.leaf >= 0 ? h.t : 0.0f;
@@ -610,7 +612,7 @@ __global__ __launch_bounds__(kBlock) void k_gen_points(DeviceScene sc, CameraTab
     d = (1.0f / sqrtf(dev::dot(d, d))) * d;
     const V3 o = v3(cam.pos[0], cam.pos[1], cam.pos[2]);
     uint32_t z0 = 0, z1 = 0;
-    const dev::Hit h = dev::trace<false>(sc, o, d, s_stack + threadIdx.x, kBlock, z0, z1);
+    const dev::Hit h = dev::trace<false>(sc, o, d, dev::lds_address(s_stack + threadIdx.x), z0, z1);
     const int64_t s = out.stride;
     float* P = out.planes;
     if (h.leaf < 0) {

@@ -216,28 +216,41 @@ __device__ __forceinline__ float half_hi(uint32_t w) {
 // plane (org + off) 2^E is fma(off, a, org a - o ix) with a = ix 2^E.
 // Returns the entry distance, or +inf when the box is missed.  An unused
 // slot (low offsets +inf, high -inf) has near distance +inf and far
-// distance -inf whatever the direction.  The current hit distance is not
+// distance -inf whatever the direction.  The bound at 0 is the z plane's, as
+// part of its FMA: the clamp modifier bounds to [0, 1], and the bound at 1
+// changes nothing that matters, as distances inside the scene are at most 1
+// (a ray that starts far outside visits more boxes, none fewer: an entry
+// distance can only shrink).  The current hit distance is not
 // clipped in here: the caller compares the entry distance with it, once
 // per child after the sort (the same boxes are visited, in the same order,
 // as with the clipped interval, for one instruction less per child).
 __device__ __forceinline__ float box_entry(float nx, float fx, float ny, float fy, float nz,
                                            float fz, float ax, float bx, float ay, float by,
                                            float az, float bz) {
-    const float tn = fmaxf(fmaxf(fmaf(nx, ax, bx), fmaf(ny, ay, by)), fmaxf(fmaf(nz, az, bz), 0.0f));
+    const float tn = fmaxf(fmaxf(fmaf(nx, ax, bx), fmaf(ny, ay, by)),
+                           __builtin_amdgcn_fmed3f(fmaf(nz, az, bz), 0.0f, 1.0f));
     const float tf = fminf(fminf(fmaf(fx, ax, bx), fmaf(fy, ay, by)), fmaf(fz, az, bz));
     return tn <= tf ? tn : INFINITY;
 }
 
-// Pop the next entry of a lane's stack into `ref` (kDone when it is
-// empty).  `top` is the lane's next free slot, `bottom` its first; slots
-// are `stride` ints apart.
-__device__ __forceinline__ void stack_pop(int32_t& ref, int32_t*& top, const int32_t* bottom,
-                                          int stride) {
-    if (top == bottom) {
-        ref = kDone;
-    } else {
-        top -= stride;
-        ref = *top;
+// A lane's stack of references in LDS, by byte address: `top` is its next
+// free slot, `bottom` its first, slots kStackStep bytes apart (lane-minor, so
+// a wave's pushes and pops hit distinct banks).
+constexpr uint32_t kStackStep = 64 * sizeof(int32_t);
+typedef __attribute__((address_space(3))) int32_t* lds_int;
+__device__ __forceinline__ uint32_t lds_address(int32_t* p) { return (uint32_t)(uintptr_t)(lds_int)p; }
+__device__ __forceinline__ void stack_push(int32_t v, uint32_t& top) {
+    *(lds_int)(uintptr_t)top = v;
+    // (an add in place after the store; moved before it, the compiler needs a
+    // second register and a copy)
+    asm volatile("v_add_u32_e32 %0, 0x100, %0" : "+v"(top) : : "memory");
+}
+// Pop the next entry into `ref` (kDone when the stack is empty).
+__device__ __forceinline__ void stack_pop(int32_t& ref, uint32_t& top, uint32_t bottom) {
+    ref = kDone;
+    if (top > bottom) {   // (an equality would have the compiler copy `bottom` about)
+        asm volatile("v_add_u32_e32 %0, 0xffffff00, %0" : "+v"(top) : : "memory");
+        ref = *(lds_int)(uintptr_t)top;
     }
 }
 
@@ -248,8 +261,8 @@ __device__ __forceinline__ void stack_pop(int32_t& ref, int32_t*& top, const int
 // (kDone when the stack is empty).  An inner reference is the node's byte
 // offset (below 2^31: the builder rejects trees of more than kMaxNodes4
 // nodes).
-__device__ __forceinline__ void node4_step(const Bvh4Node* nodes, int32_t& ref, int32_t*& top,
-                                           const int32_t* bottom, int stride, const RaySlab& r,
+__device__ __forceinline__ void node4_step(const Bvh4Node* nodes, int32_t& ref, uint32_t& top,
+                                           uint32_t bottom, const RaySlab& r,
                                            float tmax) {
     const char* nb = reinterpret_cast<const char*>(nodes);
     const uint32_t at = (uint32_t)ref | r.near_xy;
@@ -287,20 +300,17 @@ __device__ __forceinline__ void node4_step(const Bvh4Node* nodes, int32_t& ref, 
     order2(c1, c3);
     order2(c1, c2);
     if (!(key_of(c0) <= tmax)) {
-        stack_pop(ref, top, bottom, stride);
+        stack_pop(ref, top, bottom);
         return;
     }
     if (key_of(c3) <= tmax) {
-        *top = ref_of(c3);
-        top += stride;
+        stack_push(ref_of(c3), top);
     }
     if (key_of(c2) <= tmax) {
-        *top = ref_of(c2);
-        top += stride;
+        stack_push(ref_of(c2), top);
     }
     if (key_of(c1) <= tmax) {
-        *top = ref_of(c1);
-        top += stride;
+        stack_push(ref_of(c1), top);
     }
     ref = ref_of(c0);
 }
@@ -416,7 +426,7 @@ __device__ __forceinline__ float chain_key(const int4& qx, const int4& qy, const
 template <int A, int B, int C>
 __device__ __forceinline__ void chain_siblings3(const int4& qx, const int4& qy, const int4& qz,
                                                 const int4& ch, const RaySlab& r, float bx,
-                                                float by, float bz, int32_t*& top, int stride) {
+                                                float by, float bz, uint32_t& top) {
     const int32_t refs[4] = {ch.x, ch.y, ch.z, ch.w};
     Child ca = child_key(chain_key<A>(qx, qy, qz, r, bx, by, bz), refs[A]);
     Child cb = child_key(chain_key<B>(qx, qy, qz, r, bx, by, bz), refs[B]);
@@ -425,16 +435,13 @@ __device__ __forceinline__ void chain_siblings3(const int4& qx, const int4& qy, 
     order2(cb, cc);
     order2(ca, cb);
     if (key_of(cc) < INFINITY) {
-        *top = ref_of(cc);
-        top += stride;
+        stack_push(ref_of(cc), top);
     }
     if (key_of(cb) < INFINITY) {
-        *top = ref_of(cb);
-        top += stride;
+        stack_push(ref_of(cb), top);
     }
     if (key_of(ca) < INFINITY) {
-        *top = ref_of(ca);
-        top += stride;
+        stack_push(ref_of(ca), top);
     }
 }
 
@@ -443,7 +450,7 @@ __device__ __forceinline__ void chain_siblings3(const int4& qx, const int4& qy, 
 // first, as the plain step would push them (the chain's child, entered at
 // distance 0, is visited next without a push).
 __device__ __forceinline__ void chain_step(const Bvh4Node* nodes, int32_t node, int skip,
-                                           const RaySlab& r, int32_t*& top, int stride) {
+                                           const RaySlab& r, uint32_t& top) {
     const char* nb = reinterpret_cast<const char*>(nodes) + (uint32_t)node;
     const UniformNode u = uniform_node(nb);
     const int4 &qx = u.qx, &qy = u.qy, &qz = u.qz, &ch = u.ch;
@@ -452,10 +459,10 @@ __device__ __forceinline__ void chain_step(const Bvh4Node* nodes, int32_t node, 
     const float by = fmaf(og.y, r.ay, -r.oyi);
     const float bz = fmaf(og.z, r.az, -r.ozi);
     switch (skip) {
-        case 0: chain_siblings3<1, 2, 3>(qx, qy, qz, ch, r, bx, by, bz, top, stride); break;
-        case 1: chain_siblings3<0, 2, 3>(qx, qy, qz, ch, r, bx, by, bz, top, stride); break;
-        case 2: chain_siblings3<0, 1, 3>(qx, qy, qz, ch, r, bx, by, bz, top, stride); break;
-        default: chain_siblings3<0, 1, 2>(qx, qy, qz, ch, r, bx, by, bz, top, stride); break;
+        case 0: chain_siblings3<1, 2, 3>(qx, qy, qz, ch, r, bx, by, bz, top); break;
+        case 1: chain_siblings3<0, 2, 3>(qx, qy, qz, ch, r, bx, by, bz, top); break;
+        case 2: chain_siblings3<0, 1, 3>(qx, qy, qz, ch, r, bx, by, bz, top); break;
+        default: chain_siblings3<0, 1, 2>(qx, qy, qz, ch, r, bx, by, bz, top); break;
     }
 }
 
@@ -494,12 +501,12 @@ __device__ __forceinline__ void tri_test(const TriGeom* tris, int32_t i, V3 o, V
     }
 }
 
-// Closest hit along o + t d, t > 0, one ray per lane.  `stack` points at
-// this lane's first LDS stack slot; consecutive slots are `stride` ints
-// apart (lane-minor, so a wave's pushes and pops hit distinct banks).
+// Closest hit along o + t d, t > 0, one ray per lane.  `stack` is the address
+// of this lane's first LDS stack slot.
 template <bool COUNT>
-__device__ __forceinline__ Hit trace(const DeviceScene& sc, V3 o, V3 d, int32_t* stack,
-                                     int stride, uint32_t& n_nodes, uint32_t& n_tris) {
+__device__ __forceinline__ Hit trace(const DeviceScene& sc, V3 o, V3 d, uint32_t stack,
+                                     uint32_t& n_nodes, uint32_t& n_tris) {
+    d = sc.ray_unit * d;   // (a power of two: the same hits, t in that unit)
     const RaySlab r = ray_slab(o, d, sc.box_scale);
     Hit h;
     h.leaf = -1;
@@ -507,11 +514,11 @@ __device__ __forceinline__ Hit trace(const DeviceScene& sc, V3 o, V3 d, int32_t*
     h.u = h.v = 0.0f;
     int32_t best_orig = INT_MAX;
     int32_t ref = 0;
-    int32_t* top = stack;
+    uint32_t top = stack;
     while (ref != kDone) {
         if (ref >= 0) {
             if (COUNT) ++n_nodes;
-            node4_step(sc.nodes, ref, top, stack, stride, r, h.t);
+            node4_step(sc.nodes, ref, top, stack, r, h.t);
         } else {
             const int32_t lr = ~ref;
             const int32_t first = lr >> 3;
@@ -520,9 +527,10 @@ __device__ __forceinline__ Hit trace(const DeviceScene& sc, V3 o, V3 d, int32_t*
                 if (COUNT) ++n_tris;
                 tri_test(sc.tris, first + i, o, d, h, best_orig);
             }
-            stack_pop(ref, top, stack, stride);
+            stack_pop(ref, top, stack);
         }
     }
+    h.t *= sc.ray_unit;
     return h;
 }
 

@@ -239,14 +239,14 @@ __device__ __forceinline__ float tri_frame(const TriGeom* tris, int32_t i, V3& v
 
 // Radiance arriving at o along d on a refined path (Eq. 10 / 11).
 __device__ V3 refine_path(const RefineArgs& A, int64_t p, int lobe, int s, V3 o, V3 d,
-                          int32_t* stack, int n_emit) {
+                          uint32_t stack, int n_emit) {
     const DeviceScene& sc = A.b.sc;
     V3 T = v3(1.0f, 1.0f, 1.0f), C = v3(0.0f, 0.0f, 0.0f);
     float pb_prev = -1.0f;
     const bool nee = A.nee && n_emit > 0;
     uint32_t z0 = 0, z1 = 0;
     for (int vert = 1;; ++vert) {
-        const dev::Hit h = dev::trace<false>(sc, o, d, stack, kBlock, z0, z1);
+        const dev::Hit h = dev::trace<false>(sc, o, d, stack, z0, z1);
         if (h.leaf < 0) break;
         const float4 r2 = dev::load_global(reinterpret_cast<const float4*>(sc.rad + h.leaf) + 2);
         if (r2.y > 0.0f || r2.z > 0.0f || r2.w > 0.0f) {
@@ -299,7 +299,7 @@ __device__ V3 refine_path(const RefineArgs& A, int64_t p, int lobe, int s, V3 o,
             l = (1.0f / dist) * l;
             const float cz = fabsf(dev::dot(nz, l));
             if (dev::dot(ny, l) > 0.0f && cz > 0.0f) {
-                const dev::Hit sh = dev::trace<false>(sc, yo, l, stack, kBlock, z0, z1);
+                const dev::Hit sh = dev::trace<false>(sc, yo, l, stack, z0, z1);
                 if (sh.leaf == fe) {
                     const V3 fv = brdf_f(ny, wo, l, mt, a2);
                     const float pl = dist * dist * dev::rcp(cz * (float)n_emit * area);
@@ -346,7 +346,7 @@ __device__ V3 refine_path(const RefineArgs& A, int64_t p, int lobe, int s, V3 o,
 }
 
 // Refine point p with the calling wavefront (the chunked bake's layout).
-__device__ void refine_point(const RefineArgs& A, int64_t p, int lane, int32_t* stack, int n_emit) {
+__device__ void refine_point(const RefineArgs& A, int64_t p, int lane, uint32_t stack, int n_emit) {
     const BakeLaunch& b = A.b;
     const int K = b.K;
     const int P = 3 + 6 * K;
@@ -480,7 +480,7 @@ enum PathState { kIdle = 0, kTracing = 1, kFinished = 2, kHit = 3 };
 __device__ __forceinline__ bool is_leaf(int32_t ref) { return (uint32_t)ref > (uint32_t)dev::kDone; }
 using dev::kDone;
 
-__device__ void refine_point_spec(const RefineArgs& A, int64_t p, int lane, int32_t* stack, int n_emit) {
+__device__ void refine_point_spec(const RefineArgs& A, int64_t p, int lane, uint32_t stack, int n_emit) {
     const BakeLaunch& b = A.b;
     const DeviceScene& sc = b.sc;
     const int K = b.K;
@@ -548,13 +548,13 @@ __device__ void refine_point_spec(const RefineArgs& A, int64_t p, int lane, int3
     int32_t fe = -1;
     V3 cn = v3(0.0f, 0.0f, 0.0f);
     bool cont = false;
-    V3 o2 = o0, d2 = d, T2 = T;
+    V3 d2 = d, T2 = T;
     float pb2 = 0.0f;
     int next_q = 0;
 
     // traversal state of the lane's ray
     int32_t ref = kDone;
-    int32_t* top = stack;
+    uint32_t top = stack;
     dev::RaySlab rs = dev::ray_slab(o, d, sc.box_scale);
     dev::Hit h;
     h.leaf = -1;
@@ -562,6 +562,7 @@ __device__ void refine_point_spec(const RefineArgs& A, int64_t p, int lane, int3
     h.u = h.v = 0.0f;
     int32_t best_orig = INT_MAX;
     auto start_ray = [&]() {
+        d = sc.ray_unit * d;
         rs = dev::ray_slab(o, d, sc.box_scale);
         ref = 0;
         top = stack;
@@ -578,8 +579,7 @@ __device__ void refine_point_spec(const RefineArgs& A, int64_t p, int lane, int3
             if (h.leaf == fe) C = C + cn;
             shadow = false;
             if (cont) {
-                o = o2;
-                d = d2;
+                d = d2;   // (from the same point)
                 T = T2;
                 pb_prev = pb2;
                 ++vert;
@@ -593,14 +593,15 @@ __device__ void refine_point_spec(const RefineArgs& A, int64_t p, int lane, int3
             state = kFinished;
             return;
         }
+        const V3 du = sc.ray_unit_inv * d;   // the ray's unit direction
         const float4 r2 = dev::load_global(reinterpret_cast<const float4*>(sc.rad + h.leaf) + 2);
         if (r2.y > 0.0f || r2.z > 0.0f || r2.w > 0.0f) {
             float w = 1.0f;
             if (pb_prev >= 0.0f && nee) {
                 V3 v0, e1, e2, nz;
                 const float area = tri_frame(sc.tris, h.leaf, v0, e1, e2, nz);
-                const float cz = fabsf(dev::dot(nz, d));
-                const float pl = h.t * h.t * dev::rcp(cz * (float)n_emit * area);
+                const float cz = fabsf(dev::dot(nz, du)), dist = sc.ray_unit * h.t;
+                const float pl = dist * dist * dev::rcp(cz * (float)n_emit * area);
                 w = pb_prev * dev::rcp(pb_prev + pl);
             }
             C = C + v3(T.x * r2.y * w, T.y * r2.z * w, T.z * r2.w * w);
@@ -613,7 +614,7 @@ __device__ void refine_point_spec(const RefineArgs& A, int64_t p, int lane, int3
                               (double)v0.y + (double)h.u * e1.y + (double)h.v * e2.y,
                               (double)v0.z + (double)h.u * e1.z + (double)h.v * e2.z};
         const V3 y = v3((float)yd[0], (float)yd[1], (float)yd[2]);
-        const V3 wo = v3(-d.x, -d.y, -d.z);
+        const V3 wo = v3(-du.x, -du.y, -du.z);
         if (dev::dot(ny, wo) < 0.0f) ny = v3(-ny.x, -ny.y, -ny.z);
         if (!(dev::dot(ny, wo) > 0.0f)) {
             state = kFinished;
@@ -682,7 +683,6 @@ __device__ void refine_point_spec(const RefineArgs& A, int64_t p, int lane, int3
             const V3 fv = brdf_f(ny, wo, w2, mt, a2);
             const float ipb = dev::rcp(pb);
             T2 = v3(T.x * fv.x * ipb, T.y * fv.y * ipb, T.z * fv.z * ipb);
-            o2 = yo;
             d2 = w2;
             pb2 = pb;
         }
@@ -692,7 +692,7 @@ __device__ void refine_point_spec(const RefineArgs& A, int64_t p, int lane, int3
             shadow = true;
             start_ray();
         } else if (cont) {
-            o = o2;
+            o = yo;
             d = d2;
             T = T2;
             pb_prev = pb2;
@@ -800,14 +800,14 @@ __device__ void refine_point_spec(const RefineArgs& A, int64_t p, int lane, int3
             const uint64_t unparked = dev::ballot(waits) & ~dev::ballot(leaf);
             if (waits && leaf) {
                 pend = ref;
-                dev::stack_pop(ref, top, stack, kBlock);
+                dev::stack_pop(ref, top, stack);
             }
             const bool inner = ref >= 0;
             const uint64_t searching = dev::ballot(inner) & unparked;
             const int n_searching = __builtin_popcount((uint32_t)searching) +
                                     __builtin_popcount((uint32_t)(searching >> 32));
             if (searching == 0 || (n_searching < kSearchMin && (wave & ~unparked) != 0)) break;
-            if (inner) dev::node4_step(sc.nodes, ref, top, stack, kBlock, rs, h.t);
+            if (inner) dev::node4_step(sc.nodes, ref, top, stack, rs, h.t);
         }
         if (pend != kDone) {
             const int32_t lr = ~pend;
@@ -830,7 +830,7 @@ template <bool CHUNKED>
 __global__ __launch_bounds__(kBlock) FIPT_REFINE_OCCUPANCY void k_refine(RefineArgs A, int32_t* counters) {
     __shared__ int32_t s_stack[kStackSize * kBlock];
     const int lane = threadIdx.x & 63;
-    int32_t* stack = s_stack + threadIdx.x;
+    const uint32_t stack = dev::lds_address(s_stack + threadIdx.x);
     const int n_emit = __builtin_amdgcn_readfirstlane(*A.n_emit);
     uint32_t queue = dev::point_queue(A.b.n, lane);
     for (int64_t p; (p = dev::next_point(queue, counters, A.b.n, lane)) >= 0;) {
