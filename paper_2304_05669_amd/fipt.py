@@ -180,9 +180,14 @@ def _check(rc: int, allow=()):
 
 
 def _stream(stream=None):
-    if stream is None:
-        stream = torch.cuda.current_stream()
-    return C.c_void_p(stream.cuda_stream)
+    """The raw handle of ``stream``, by default torch's current stream on the
+    current device (read without building a Stream object: 0.2 against 3 us,
+    of 8 to 15 us for a whole call)."""
+    if stream is not None:
+        return stream.cuda_stream
+    if not torch.cuda.is_initialized():
+        torch.cuda.init()
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _dev(t: torch.Tensor, dtype, name: str) -> int:
@@ -198,16 +203,13 @@ def _dev(t: torch.Tensor, dtype, name: str) -> int:
 def _need(t: torch.Tensor, shape, name: str):
     """Reject a caller buffer whose shape differs from what the kernel writes
     or reads (the C entry points take bare pointers)."""
-    if not isinstance(t, torch.Tensor) or tuple(t.shape) != tuple(shape):
+    if not isinstance(t, torch.Tensor) or t.shape != tuple(shape):
         got = tuple(t.shape) if isinstance(t, torch.Tensor) else type(t).__name__
         raise ValueError(f"{name} must have shape {tuple(shape)}, got {got}")
 
 
 def _f32_array(v, n):
-    a = (C.c_float * n)()
-    for i, x in enumerate(v):
-        a[i] = float(x)
-    return a
+    return (C.c_float * n)(*map(float, v))
 
 
 def version() -> int:
@@ -565,6 +567,12 @@ def fipt_hbm_stream(kind: int, a: torch.Tensor, c: torch.Tensor, b: torch.Tensor
     return c
 
 
+def _factor(go: torch.Tensor):
+    """An incoming loss gradient as the one double fipt_scale_by takes."""
+    f = go.reshape(1)
+    return f if f.dtype == torch.float64 and f.is_contiguous() else f.to(torch.float64).contiguous()
+
+
 class FactoredLoss(torch.autograd.Function):
     """loss = sum (Gamma(Lr(material)) - Gamma(Lgt))^2 with the hand-written
     gradient of the library; differentiable in ``material`` [5, n]."""
@@ -579,7 +587,7 @@ class FactoredLoss(torch.autograd.Function):
     @staticmethod
     def backward(ctx, go):
         (grad,) = ctx.saved_tensors
-        g = fipt_scale_by(grad, go.reshape(1).to(torch.float64).contiguous())
+        g = fipt_scale_by(grad, _factor(go))
         return g, None, None, None, None
 
 
@@ -600,7 +608,7 @@ class MaskedFactoredLoss(torch.autograd.Function):
     @staticmethod
     def backward(ctx, go):
         grad, galpha = ctx.saved_tensors
-        f = go.reshape(1).to(torch.float64).contiguous()
+        f = _factor(go)
         gm = fipt_scale_by(grad, f) if grad.numel() else None
         ga = fipt_scale_by(galpha, f) if galpha.numel() else None
         return gm, ga, None, None, None, None, None
