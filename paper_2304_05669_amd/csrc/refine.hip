@@ -470,10 +470,20 @@ __device__ void refine_point(const RefineArgs& A, int64_t p, int lane, uint32_t 
 // of the point in lane order (a ballot), so the schedule, and the result,
 // depend only on the inputs.  Each path's arithmetic and random numbers are
 // those of refine_path.
-constexpr int kRefillMin = 40;
+//
+// The three thresholds trade idle lanes against masked ones.  A path's shading
+// (process_hit: the surface, the factor lookup, a sample, an emitter test) is
+// far more instructions than a node step, so it pays to run it for many lanes
+// at once and let them wait; a refill is cheap beside it and fills lanes that
+// would idle for the rest of several segments.  76,800 points of the 65,536-
+// triangle room, 64 paths for each of 7 lobes, ms per pass for (refill, hit,
+// search): (40, 16, 8) 33.2, (24, 16, 8) 30.1, (24, 24, 8) 28.8, (16, 24, 10)
+// 28.3, (16, 32, 12) 27.4, (12, 40, 12) 26.8, (8, 40, 10) 26.5, (20, 40, 14)
+// 28.1, (12, 48, 16) 27.7, (4, 36, 12) 27.0.
+constexpr int kRefillMin = 8;      // free lanes that trigger a refill
 constexpr int kRefillMaxK = 10;
-constexpr int kHitMin = 16;        // ended rays processed together once this many wait
-constexpr int kSearchMin = 8;      // leave the node loop below this many searchers
+constexpr int kHitMin = 40;        // ended rays processed together once this many wait
+constexpr int kSearchMin = 10;     // leave the node loop below this many searchers
 enum PathState { kIdle = 0, kTracing = 1, kFinished = 2, kHit = 3 };
 
 // A leaf reference: negative but not kDone (INT_MIN).
