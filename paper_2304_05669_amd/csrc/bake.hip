@@ -6,8 +6,8 @@
 // (lobe, sample) pairs of that point, flattened over the diffuse lobe and
 // the K specular levels, so the lanes of a wave share the ray origin and
 // start traversal on the same nodes.  After each chunk of 64 samples the
-// contributions of every lobe present in the chunk are summed by a fixed
-// xor butterfly; each lane keeps the running sums of two accumulator slots
+// contributions of every lobe present in the chunk are summed in a fixed
+// order; each lane keeps the running sums of two accumulator slots
 // in registers.  The summation order depends only on the sample counts, so
 // a point's result is bitwise independent of which launch, tile or batch it
 // was baked in.
@@ -143,22 +143,15 @@ __device__ __forceinline__ void bake_point(const BakeLaunch& b, const float* sig
         const int l_last = lobe_of(min(q0 + 63, S - 1), spp_d, spp_s);
         for (int l = l_first; l <= l_last; ++l) {
             const bool mine = lobe == l;
-            const float r0 = dev::wave_sum(mine ? c0 : 0.0f);
-            const float r1 = dev::wave_sum(mine ? c1 : 0.0f);
-            const float r2 = dev::wave_sum(mine ? c2 : 0.0f);
             const int base = l == 0 ? 0 : 3 + 6 * (l - 1);
-            float r3 = 0.0f, r4 = 0.0f, r5 = 0.0f;
-            if (l > 0) {
-                r3 = dev::wave_sum(mine ? c3 : 0.0f);
-                r4 = dev::wave_sum(mine ? c4 : 0.0f);
-                r5 = dev::wave_sum(mine ? c5 : 0.0f);
-            }
             const int na = lane - base, nb = lane + 64 - base;
-            const float ra = na == 0 ? r0 : na == 1 ? r1 : na == 2 ? r2 : na == 3 ? r3 : na == 4 ? r4 : r5;
-            const float rb = nb == 0 ? r0 : nb == 1 ? r1 : nb == 2 ? r2 : nb == 3 ? r3 : nb == 4 ? r4 : r5;
+            const float m0 = mine ? c0 : 0.0f, m1 = mine ? c1 : 0.0f, m2 = mine ? c2 : 0.0f;
+            const float m3 = mine ? c3 : 0.0f, m4 = mine ? c4 : 0.0f, m5 = mine ? c5 : 0.0f;
+            // (a lane's two slots are 64 apart: at most one is in this lobe)
+            const float total = dev::lobe_sum(l > 0, m0, m1, m2, m3, m4, m5, na >= 0 && na < 6 ? na : nb);
             const int width = l == 0 ? 3 : 6;
-            if (na >= 0 && na < width) acc_a += ra;
-            if (nb >= 0 && nb < width) acc_b += rb;
+            if (na >= 0 && na < width) acc_a += total;
+            if (nb >= 0 && nb < width) acc_b += total;
         }
     }
     if (lane < P) {
@@ -183,7 +176,7 @@ __device__ __forceinline__ void bake_point(const BakeLaunch& b, const float* sig
 // reaches a leaf parks it and keeps descending while other lanes are still
 // looking for theirs; once only a few lanes are still searching, all lanes
 // test their parked leaves together.
-// At the end of the point one fixed butterfly sums the accumulators.
+// At the end of the point the accumulators are summed in a fixed order.
 constexpr int kRefillMaxK = 10;      // 3 + 6K output slots fit the 64 lanes
 using dev::kDone;
 constexpr int kRefillMin = 40;       // refill once this many lanes are free
@@ -236,7 +229,7 @@ __device__ __forceinline__ void bake_point_refill(const BakeLaunch& b, const flo
     // its contributions for its current lobe in cur[]; a lane's lobes only
     // increase (samples are handed out in order), so when it moves on, its
     // partial sums for the old lobe are flushed: all lanes leaving the same
-    // lobe at once are summed by the fixed butterfly and the owners add the
+    // lobe at once are summed in a fixed order and the owners add the
     // totals.  Everything depends only on the inputs, so results are
     // reproducible bit for bit.
     float own = 0.0f;
@@ -246,21 +239,13 @@ __device__ __forceinline__ void bake_point_refill(const BakeLaunch& b, const flo
         uint64_t m = dev::ballot(need);
         while (m) {
             const int leader = __ffsll((unsigned long long)m) - 1;
-            const int l = __shfl(cur_lobe, leader, 64);
+            const int l = __builtin_amdgcn_readlane(cur_lobe, leader);
             const bool in = need && cur_lobe == l;
             m &= ~dev::ballot(in);
-            const float s0 = dev::wave_sum(in ? cur0 : 0.0f);
-            const float s1 = dev::wave_sum(in ? cur1 : 0.0f);
-            const float s2 = dev::wave_sum(in ? cur2 : 0.0f);
-            float s3 = 0.0f, s4 = 0.0f, s5 = 0.0f;
-            if (l > 0) {
-                s3 = dev::wave_sum(in ? cur3 : 0.0f);
-                s4 = dev::wave_sum(in ? cur4 : 0.0f);
-                s5 = dev::wave_sum(in ? cur5 : 0.0f);
-            }
             const int r = lane - (l == 0 ? 0 : 3 + 6 * (l - 1));
-            if (r >= 0 && r < (l == 0 ? 3 : 6))
-                own += r == 0 ? s0 : r == 1 ? s1 : r == 2 ? s2 : r == 3 ? s3 : r == 4 ? s4 : s5;
+            const float total = dev::lobe_sum(l > 0, in ? cur0 : 0.0f, in ? cur1 : 0.0f, in ? cur2 : 0.0f,
+                                              in ? cur3 : 0.0f, in ? cur4 : 0.0f, in ? cur5 : 0.0f, r);
+            if (r >= 0 && r < (l == 0 ? 3 : 6)) own += total;
         }
     };
 

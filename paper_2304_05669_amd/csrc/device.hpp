@@ -587,12 +587,52 @@ __device__ __forceinline__ V3 radiance_voxel(const DeviceScene& sc, const Hit& h
 // int-valued __ballot costs two extra instructions per call).
 __device__ __forceinline__ uint64_t ballot(bool p) { return __builtin_amdgcn_ballot_w64(p); }
 
-// Sum over the 64 lanes of a wave by a fixed xor butterfly: every lane ends
-// with the same, order-fixed total.
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) v += __shfl_xor(v, m, 64);
-    return v;
+// Sum over the wavefront of component `want` (a lane's own choice; 3 to 5 only
+// if `six`) of the lanes' c0 ... c5.  The lane totals a point's lobes are
+// folded into its output slots with, so the order is fixed: lanes 32 apart,
+// 16 apart, then within 16 lanes by 1, 2, 4 and 8.
+// The first two levels swap halves of two registers (v_permlane32_swap,
+// v_permlane16_swap) and so fold two components with one add each; the
+// others are adds with a DPP operand.  About 30 vector instructions for six
+// components, without LDS; a butterfly of shuffles per component was 36 LDS
+// instructions and as many adds, six deep.  Bake of 4,096 points x 448 samples
+// 70.9 -> 63.9 us, of 10,007 x 139 191 -> 179 us, 614,400 x 112 with its
+// pooling 7.16 -> 6.84 ms, the room's step (896 samples) 107.6 -> 106.6 ms.
+template <int PATTERN>
+__device__ __forceinline__ float dpp_add(float v) {
+    return v + __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(v), PATTERN, 0xF, 0xF, true));
+}
+__device__ __forceinline__ float fold32(float a, float b) {   // lanes 0-31: a, 32-63: b
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ float fold16(float a, float b) {   // even rows of 16 lanes: a, odd: b
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ float fold_row(float v) {
+    v = dpp_add<0xB1>(v);           // quad_perm [1, 0, 3, 2]
+    v = dpp_add<0x4E>(v);           // quad_perm [2, 3, 0, 1]
+    v = dpp_add<0x141>(v);          // row_half_mirror: the other quad of 8 lanes
+    return dpp_add<0x140>(v);       // row_mirror: the other 8 of 16 lanes
+}
+__device__ __forceinline__ float lane_value(float v, int lane) {
+    return __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(v), lane));
+}
+__device__ __forceinline__ float lobe_sum(bool six, float c0, float c1, float c2, float c3, float c4, float c5,
+                                          int want) {
+    const float v01 = fold32(c0, c1);
+    if (!six) {
+        const float u = fold_row(fold16(v01, fold32(c2, c2)));   // rows: c0 c2 c1 c2
+        const float s0 = lane_value(u, 0), s2 = lane_value(u, 16), s1 = lane_value(u, 32);
+        return want == 0 ? s0 : want == 1 ? s1 : s2;
+    }
+    const float v45 = fold32(c4, c5);
+    const float u = fold_row(fold16(v01, fold32(c2, c3)));       // rows: c0 c2 c1 c3
+    const float w = fold_row(fold16(v45, v45));                  // rows: c4 c4 c5 c5
+    const float s0 = lane_value(u, 0), s2 = lane_value(u, 16), s1 = lane_value(u, 32), s3 = lane_value(u, 48);
+    const float s4 = lane_value(w, 0), s5 = lane_value(w, 32);
+    return want == 0 ? s0 : want == 1 ? s1 : want == 2 ? s2 : want == 3 ? s3 : want == 4 ? s4 : s5;
 }
 
 // ---- work distribution shared by the persistent bake kernels ---------------
