@@ -677,7 +677,10 @@ __global__ __launch_bounds__(kAdjBlock) void k_grid_adjoint_sums(GridPlanDev P,
         for (int ch = 0; ch < C; ++ch) acc[ch][i] = 0;
         bad[i] = 0;
     }
-    const int32_t ci = unit.y + tid;
+    // (a wavefront takes every fourth column: neighbours are mostly of one
+    // cell and their integer adds meet in the same nodes: 53.2 -> 48.3 us at
+    // 1.84 M points on 128^3 nodes, 14.0 -> 12.9 us at 8,192 on 32^3)
+    const int32_t ci = unit.y + (tid & 63) * (kAdjBlock / 64) + (tid >> 6);
     const bool live = ci < unit.z;
     float v[8][C];
     float m[C];
