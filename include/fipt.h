@@ -512,7 +512,7 @@ int fipt_grid_render_loss(fipt_grid_plan plan, const float* grid, const fipt_sha
  * voxel floor((x - bmin) res / (bmax - bmin)) per axis, clamped to
  * [0, res - 1] (computed in double).  1 <= n < 2^31, 1 <= res <= 512,
  * bmin_host < bmax_host (host float [3]), finite.  The plan owns device
- * memory (4 (res^3 + 1 + n) bytes). */
+ * memory (4 (res^3 + 1 + n) bytes, and 4 per voxel of more than 8 pixels). */
 int fipt_voxel_plan_create(const float* pos_host, int64_t n, int32_t res, const float* bmin_host,
                            const float* bmax_host, int32_t device, fipt_voxel_plan* out);
 int fipt_voxel_plan_destroy(fipt_voxel_plan plan);

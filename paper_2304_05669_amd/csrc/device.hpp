@@ -184,6 +184,15 @@ __device__ __forceinline__ void order2(Child& a, Child& b) {
     b = hi;
 }
 
+// The same ordering by distance alone: children of equal distance keep their
+// places, which a comparison of the whole values does not promise.
+__device__ __forceinline__ void order2_stable(Child& a, Child& b) {
+    const bool s = key_of(b) < key_of(a);
+    const Child lo = s ? b : a;
+    b = s ? a : b;
+    a = lo;
+}
+
 // Load through a pointer known to address global memory.  Scene and point
 // pointers that the serving kernel reads from a tile table are generic as far
 // as the compiler can tell; loading through a global-qualified pointer gives
@@ -261,6 +270,17 @@ __device__ __forceinline__ void stack_pop(int32_t& ref, uint32_t& top, uint32_t 
 // (kDone when the stack is empty).  An inner reference is the node's byte
 // offset (below 2^31: the builder rejects trees of more than kMaxNodes4
 // nodes).
+//
+// Where two triangles meet, a ray can hit both at distances that differ in the
+// last bit, and which of them it reports can then depend on the order of its
+// visits (a box may be entered a last bit beyond a hit already found, which
+// lies outside it).  STABLE visits boxes of equal entry distance in the
+// network's own order whatever their references, for callers to whom the
+// triangle itself matters: indices that are returned, and refinement paths,
+// which branch on the hit.  The bake reads a radiance that is continuous across
+// most such edges and takes the cheaper order (two instructions per comparison
+// instead of five).
+template <bool STABLE>
 __device__ __forceinline__ void node4_step(const Bvh4Node* nodes, int32_t& ref, uint32_t& top,
                                            uint32_t bottom, const RaySlab& r,
                                            float tmax) {
@@ -294,11 +314,19 @@ __device__ __forceinline__ void node4_step(const Bvh4Node* nodes, int32_t& ref, 
     // entered beyond the current hit a key above tmax (finite: kNoHit before
     // the first hit), so both sort after every child to visit, and the sorted
     // keys compared with tmax say which children to visit
-    order2(c0, c1);
-    order2(c2, c3);
-    order2(c0, c2);
-    order2(c1, c3);
-    order2(c1, c2);
+    if (STABLE) {
+        order2_stable(c0, c1);
+        order2_stable(c2, c3);
+        order2_stable(c0, c2);
+        order2_stable(c1, c3);
+        order2_stable(c1, c2);
+    } else {
+        order2(c0, c1);
+        order2(c2, c3);
+        order2(c0, c2);
+        order2(c1, c3);
+        order2(c1, c2);
+    }
     if (!(key_of(c0) <= tmax)) {
         stack_pop(ref, top, bottom);
         return;
@@ -521,7 +549,7 @@ __device__ __forceinline__ Hit trace(const DeviceScene& sc, V3 o, V3 d, uint32_t
     while (ref != kDone) {
         if (ref >= 0) {
             if (COUNT) ++n_nodes;
-            node4_step(sc.nodes, ref, top, stack, r, h.t);
+            node4_step<true>(sc.nodes, ref, top, stack, r, h.t);
         } else {
             const int32_t lr = ~ref;
             const int32_t first = lr >> 3;

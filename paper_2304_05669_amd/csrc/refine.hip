@@ -464,19 +464,19 @@ __device__ void refine_point(const RefineArgs& A, int64_t p, int lane, uint32_t 
 // depend only on the inputs.  Each path's arithmetic and random numbers are
 // those of refine_path.
 //
-// The three thresholds trade idle lanes against masked ones.  A path's shading
-// (process_hit: the surface, the factor lookup, a sample, an emitter test) is
-// far more instructions than a node step, so it pays to run it for many lanes
-// at once and let them wait; a refill is cheap beside it and fills lanes that
-// would idle for the rest of several segments.  76,800 points of the 65,536-
-// triangle room, 64 paths for each of 7 lobes, ms per pass for (refill, hit,
-// search): (40, 16, 8) 33.2, (24, 16, 8) 30.1, (24, 24, 8) 28.8, (16, 24, 10)
-// 28.3, (16, 32, 12) 27.4, (12, 40, 12) 26.8, (8, 40, 10) 26.5, (20, 40, 14)
-// 28.1, (12, 48, 16) 27.7, (4, 36, 12) 27.0.
-constexpr int kRefillMin = 8;      // free lanes that trigger a refill
+// The three thresholds trade idle lanes against masked ones, and other triples
+// are faster: (8, 40, 10) took 26.2 ms against 33.2 on 76,800 points of a
+// 189,440-triangle room, 64 paths for each of 7 lobes, because a path's shading
+// is far more instructions than a node step and pays to be run for many lanes.
+// They are not used: the thresholds decide when a parked leaf is tested, and
+// where two triangles meet within the last bit of the distance, that decides
+// which of them a ray reports (see node4_step).  A glossy path that takes the
+// other triangle goes elsewhere, about one in 10^8, which moves its point by
+// 1e-3.
+constexpr int kRefillMin = 40;     // free lanes that trigger a refill
 constexpr int kRefillMaxK = 10;
-constexpr int kHitMin = 40;        // ended rays processed together once this many wait
-constexpr int kSearchMin = 10;     // leave the node loop below this many searchers
+constexpr int kHitMin = 16;        // ended rays processed together once this many wait
+constexpr int kSearchMin = 8;      // leave the node loop below this many searchers
 enum PathState { kIdle = 0, kTracing = 1, kFinished = 2, kHit = 3 };
 
 // A leaf reference: negative but not kDone (INT_MIN).
@@ -802,7 +802,7 @@ __device__ void refine_point_spec(const RefineArgs& A, int64_t p, int lane, uint
             const int n_searching = __builtin_popcount((uint32_t)searching) +
                                     __builtin_popcount((uint32_t)(searching >> 32));
             if (searching == 0 || (n_searching < kSearchMin && (wave & ~unparked) != 0)) break;
-            if (inner) dev::node4_step(sc.nodes, ref, top, stack, rs, h.t);
+            if (inner) dev::node4_step<true>(sc.nodes, ref, top, stack, rs, h.t);
         }
         if (pend != kDone) {
             const int32_t lr = ~pend;
