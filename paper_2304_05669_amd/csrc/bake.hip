@@ -390,7 +390,7 @@ __device__ __forceinline__ void bake_point_refill(const BakeLaunch& b, const flo
             if (COUNT && lane == 0) ++n_node_steps;
             if (inner) {
                 if (COUNT) ++n_nodes;
-                dev::node4_step<false>(sc.nodes, ref, top, stack, rs, h.t);
+                dev::node4_step(sc.nodes, ref, top, stack, rs, h.t);
             }
         }
         // ---- leaves ---------------------------------------------------------

@@ -87,8 +87,7 @@ struct Wide4 {
 // and y planes are held once for each pair of directions (piece s: the planes
 // entered by a ray going down x if s & 1 and down y if s & 2; the planes it
 // leaves by are piece 3 - s) and the z planes in both orders.  The child
-// references and the origin share two pieces such that each reference has a
-// free word after it (see node4_step).
+// references and the origin share two pieces.
 struct alignas(16) Bvh4Node {
     uint16_t xy[4][8];   // bytes 0..63: x planes of the four slots, y planes
     uint16_t z[2][8];    // bytes 64..95: lows and highs, highs and lows

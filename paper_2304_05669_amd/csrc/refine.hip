@@ -470,7 +470,7 @@ __device__ void refine_point(const RefineArgs& A, int64_t p, int lane, uint32_t 
 // is far more instructions than a node step and pays to be run for many lanes.
 // They are not used: the thresholds decide when a parked leaf is tested, and
 // where two triangles meet within the last bit of the distance, that decides
-// which of them a ray reports (see node4_step).  A glossy path that takes the
+// which of them a ray reports (see order2).  A glossy path that takes the
 // other triangle goes elsewhere, about one in 10^8, which moves its point by
 // 1e-3.
 constexpr int kRefillMin = 40;     // free lanes that trigger a refill
@@ -802,7 +802,7 @@ __device__ void refine_point_spec(const RefineArgs& A, int64_t p, int lane, uint
             const int n_searching = __builtin_popcount((uint32_t)searching) +
                                     __builtin_popcount((uint32_t)(searching >> 32));
             if (searching == 0 || (n_searching < kSearchMin && (wave & ~unparked) != 0)) break;
-            if (inner) dev::node4_step<true>(sc.nodes, ref, top, stack, rs, h.t);
+            if (inner) dev::node4_step(sc.nodes, ref, top, stack, rs, h.t);
         }
         if (pend != kDone) {
             const int32_t lr = ~pend;
