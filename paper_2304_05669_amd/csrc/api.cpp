@@ -185,13 +185,6 @@ int fipt_scene_create(const float* verts, int64_t n_verts, const int32_t* tris, 
         s->bmin[k] = bvh.bmin[k];
         s->bmax[k] = bvh.bmax[k];
     }
-    double diag2 = 0.0;
-    for (int k = 0; k < 3; ++k) {
-        const double ext = (double)bvh.bmax[k] - (double)bvh.bmin[k];
-        diag2 += ext * ext;
-    }
-    const double unit_exp = diag2 > 0.0 ? std::ceil(0.5 * std::log2(diag2)) : 0.0;
-    s->ray_unit = (float)std::ldexp(1.0, (int)std::min(std::max(unit_exp, -20.0), 20.0));
     hipStream_t st = (hipStream_t)stream;
     if ((rc = dev_alloc(&s->d_nodes, bvh.nodes4.size(), &s->bytes)) ||
         (rc = dev_alloc(&s->d_tris, bvh.tris.size(), &s->bytes)) ||

@@ -337,7 +337,6 @@ __device__ __forceinline__ void bake_point_refill(const BakeLaunch& b, const flo
                         }
                         if (shoot) {
                             if (COUNT) ++n_rays;
-                            d = sc.ray_unit * d;
                             rs = dev::ray_slab(o, d, sc.box_scale);
                             // start below the point's chain: its siblings
                             // the ray hits are pushed level by level
@@ -458,7 +457,6 @@ __device__ __forceinline__ BakeLaunch uniform_job(const BakeLaunch& j) {
     b.sc.rad = static_cast<const TriRad*>(up(j.sc.rad));
     b.sc.n_tris = wave_uniform(j.sc.n_tris);
     b.sc.box_scale = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(j.sc.box_scale)));
-    b.sc.ray_unit = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(j.sc.ray_unit)));
     b.sc.vox = nullptr;   // serving scenes have no voxel cache
     b.sc.vox_res = 0;
     b.pts = static_cast<const float*>(up(j.pts));

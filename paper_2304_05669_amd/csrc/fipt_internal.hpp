@@ -154,10 +154,6 @@ struct DeviceScene {
     const TriRad* rad;
     int64_t n_tris;
     float box_scale;   // 2^E: the unit of the node bounds
-    // Rays are traced with directions of length ray_unit, a power of two no
-    // less than the diagonal of the scene's box (within 2^-20 .. 2^20), so
-    // distances along them inside the scene lie in [0, 1] (see box_entry).
-    float ray_unit, ray_unit_inv;
     // Voxel radiance cache (NULL unless the scene uses one), stored sparse in
     // bricks of 4 x 4 x 4 voxels: voxel (i, j, k) belongs to brick
     // (i / 4, j / 4, k / 4), numbered (bz B + by) B + bx with B = ceil(R / 4),
@@ -354,7 +350,6 @@ struct fipt_scene_s {
     int32_t max_depth = 0;
     int32_t cache_kind = -1;
     float box_scale = 1.0f;        // 2^E of the node bounds
-    float ray_unit = 1.0f;         // see DeviceScene
     float bmin[3] = {0, 0, 0}, bmax[3] = {0, 0, 0};
     fipt::Bvh4Node* d_nodes = nullptr;   // 4-wide nodes
     fipt::TriGeom* d_tris = nullptr;
@@ -382,7 +377,7 @@ struct fipt_scene_s {
     std::atomic<int> refs{0};      // serving requests referencing the scene
     fipt::DeviceScene view() const {
         const bool vox = cache_kind == FIPT_CACHE_VOXEL;
-        return {d_nodes, d_tris, d_rad, n_tris, box_scale, ray_unit, 1.0f / ray_unit, vox ? d_vox_words : nullptr,
+        return {d_nodes, d_tris, d_rad, n_tris, box_scale, vox ? d_vox_words : nullptr,
                 vox ? d_vox : nullptr, vox ? vox_res : 0, vox ? (vox_res + 3) / 4 : 0,
                 {vox_lo[0], vox_lo[1], vox_lo[2]}, {vox_scale[0], vox_scale[1], vox_scale[2]}};
     }

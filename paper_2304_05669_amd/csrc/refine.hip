@@ -557,7 +557,6 @@ __device__ void refine_point_spec(const RefineArgs& A, int64_t p, int lane, uint
     h.u = h.v = 0.0f;
     int32_t best_orig = INT_MAX;
     auto start_ray = [&]() {
-        d = sc.ray_unit * d;
         rs = dev::ray_slab(o, d, sc.box_scale);
         ref = 0;
         top = stack;
@@ -588,15 +587,14 @@ __device__ void refine_point_spec(const RefineArgs& A, int64_t p, int lane, uint
             state = kFinished;
             return;
         }
-        const V3 du = sc.ray_unit_inv * d;   // the ray's unit direction
         const float4 r2 = dev::load_global(reinterpret_cast<const float4*>(sc.rad + h.leaf) + 2);
         if (r2.y > 0.0f || r2.z > 0.0f || r2.w > 0.0f) {
             float w = 1.0f;
             if (pb_prev >= 0.0f && nee) {
                 V3 v0, e1, e2, nz;
                 const float area = tri_frame(sc.tris, h.leaf, v0, e1, e2, nz);
-                const float cz = fabsf(dev::dot(nz, du)), dist = sc.ray_unit * h.t;
-                const float pl = dist * dist * dev::rcp(cz * (float)n_emit * area);
+                const float cz = fabsf(dev::dot(nz, d));
+                const float pl = h.t * h.t * dev::rcp(cz * (float)n_emit * area);
                 w = pb_prev * dev::rcp(pb_prev + pl);
             }
             C = C + v3(T.x * r2.y * w, T.y * r2.z * w, T.z * r2.w * w);
@@ -609,7 +607,7 @@ __device__ void refine_point_spec(const RefineArgs& A, int64_t p, int lane, uint
                               (double)v0.y + (double)h.u * e1.y + (double)h.v * e2.y,
                               (double)v0.z + (double)h.u * e1.z + (double)h.v * e2.z};
         const V3 y = v3((float)yd[0], (float)yd[1], (float)yd[2]);
-        const V3 wo = v3(-du.x, -du.y, -du.z);
+        const V3 wo = v3(-d.x, -d.y, -d.z);
         if (dev::dot(ny, wo) < 0.0f) ny = v3(-ny.x, -ny.y, -ny.z);
         if (!(dev::dot(ny, wo) > 0.0f)) {
             state = kFinished;
