@@ -48,8 +48,8 @@ constexpr int kW1 = kHid * kIn, kW2 = kHid * kHid, kW3 = kOut * kHid;
 constexpr int kWeights = kW1 + kW2 + kW3;   // 8512
 constexpr int kBlock = 256;
 // the workspace: 325 floats per point beside the feature gradients and 12,288
-// per 2048 points, of which the encoding (64 per point) and the workgroups'
-// weight gradients are used
+// per 2048 points, of which the encoding (64 per point) and the runs' weight
+// gradients are used
 constexpr int kChunk = 2048;
 constexpr int kWsRows = 3 * 64 + 2 * 64 + kOut;
 constexpr int kFeatGradRows = kLevels * kFeat;     // per-level feature gradients, [32][n] float2
@@ -152,9 +152,11 @@ __device__ __forceinline__ void load_weights(const float* __restrict__ params, f
 // written [feature][point] from the accumulators and read by rows (B of the
 // next layer) or by columns (both operands of a weight gradient, whose
 // reduction runs over the points).  A tile's own pre-activations stay in
-// registers as the ReLU masks.  The weight gradients of all the workgroup's
-// points accumulate in 36 registers and leave once, at its end.  The products
-// that decide the masks (z1, z2) are formed as in the forward pass.
+// registers as the ReLU masks.  The weight gradients accumulate in 36 registers
+// over a run of consecutive tiles and leave at its end.  Runs are cut from the
+// number of points alone (see BackwardRuns): at most 2,048 points, so that a
+// single-precision chain has a bound, and as many for all workgroups.  The
+// products that decide the masks (z1, z2) are formed as in the forward pass.
 // Bound by the single-precision matrix rate: 200 products of 64 cycles per
 // wavefront and 64 points, 0.6 ms on the room's 1,843,200 points.  It takes
 // 1.01 ms there (two wavefronts per SIMD, 69 KB of LDS per workgroup, and the
@@ -200,7 +202,7 @@ __device__ __forceinline__ v16f zero16() {
 
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 8))) void k_hg_backward(
     HgArgs a, const float* __restrict__ gy, int64_t gs, const float* __restrict__ ws, int64_t wn,
-    float2* __restrict__ fgrad, float* __restrict__ part) {
+    float2* __restrict__ fgrad, float* __restrict__ part, int run_tiles, int n_runs) {
     __shared__ float w[kLdsW];
     __shared__ float Q[kHid * kWs];            // h1, then d1
     __shared__ float R[kHid * kWs];            // h2, then d2, then the encoding
@@ -222,11 +224,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 8))) 
     const float* Rcol = R + 4 * h * kWs + 32 * j + lo;
     float* Qout = Q + (32 * u + 4 * h) * kWs + 32 * j + lo;   // accumulator register r at row dfeat(0, r, 0)
     float* Rout = R + (32 * u + 4 * h) * kWs + 32 * j + lo;
-    v16f dw1 = zero16(), dw2 = zero16();
-    v4f dw3;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) dw3[r] = 0.0f;
-    const int64_t step = (int64_t)gridDim.x * kTilePts;
+    const int64_t run_pts = (int64_t)run_tiles * kTilePts;
     float e[kLevels];   // the next tile's encoding: feature 2 l + h of this lane's point
     auto fetch = [&](int64_t base) {
         const int64_t pt = base + 32 * j + lo;
@@ -238,121 +236,133 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 8))) 
             for (int l = 0; l < kLevels; ++l) e[l] = 0.0f;
         }
     };
-    fetch((int64_t)blockIdx.x * kTilePts);
-    for (int64_t base = (int64_t)blockIdx.x * kTilePts; base < a.n; base += step) {
-        asm volatile("" ::: "memory");   // (the weights are read from LDS where they are used)
-        const int64_t pt = base + 32 * j + lo;   // this lane's point in a tile
-        // z1 = W1 e
-        v16f z = zero16();
-        product<kLevels>(z, [&](int l) { return W1row[2 * l]; }, [&](int l) { return e[l]; });
-        __syncthreads();   // (the previous tile's reads of Q and R)
+    fetch(blockIdx.x * run_pts);
+    for (int run = (int)blockIdx.x; run < n_runs; run += (int)gridDim.x) {
+        const int64_t end = min(a.n, (run + 1) * run_pts);
+        v16f dw1 = zero16(), dw2 = zero16();
+        v4f dw3;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            z[r] = fmaxf(z[r], 0.0f);
-            Qout[dfeat(0, r, 0) * kWs] = z[r];
-        }
-        __syncthreads();
-        // z2 = W2 h1
-        v16f y = zero16();
-        product<32>(y, [&](int k) { return W2row[dfeat(k >> 4, k & 15, 0)]; },
-                    [&](int k) { return Qcol[dfeat(k >> 4, k & 15, 0) * kWs]; });
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            y[r] = fmaxf(y[r], 0.0f);
-            Rout[dfeat(0, r, 0) * kWs] = y[r];
-        }
-        __syncthreads();
-        // outputs o = wave (and 4 on the first wavefront): each lane sums its
-        // half of the features of two points, the halves meet with a swap
-        for (int o = wave; o < kOut; o += kBlock / 64) {
-            float s0 = 0.0f, s1 = 0.0f;
-            const float* w3 = W3 + o * kHid + 4 * h;
-            const float* hr = R + 4 * h * kWs + lo;
-#pragma unroll
-            for (int k = 0; k < 32; ++k) {
-                const int c = dfeat(k >> 4, k & 15, 0);
-                s0 = fmaf(w3[c], hr[c * kWs], s0);
-                s1 = fmaf(w3[c], hr[c * kWs + 32], s1);
-                if ((k & 7) == 7) __builtin_amdgcn_sched_barrier(0);
-            }
-            float pa, pb;
-            swap_halves(s0, s1, pa, pb);
-            const float yv = 1.0f / (1.0f + expf(-(pa + pb)));
-            const int64_t i = base + lane;
-            D3[o][lane] = i < a.n ? gy[o * gs + i] * yv * (1.0f - yv) : 0.0f;
-        }
-        __syncthreads();
-        // dW3 += d3 h2^T (16 columns per wavefront); d2 = (W3^T d3) masked
-#pragma unroll
-        for (int k0 = 0; k0 < kTilePts; k0 += 4) {
-            const float av = l16 < kOut ? D3[l16 < kOut ? l16 : 0][k0 + k16] : 0.0f;
-            dw3 = __builtin_amdgcn_mfma_f32_16x16x4f32(av, R[(16 * wave + l16) * kWs + k0 + k16], dw3, 0, 0, 0);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        {
-            float d3[kOut];
-#pragma unroll
-            for (int o = 0; o < kOut; ++o) d3[o] = D3[o][32 * j + lo];
+        for (int r = 0; r < 4; ++r) dw3[r] = 0.0f;
+        for (int64_t base = run * run_pts; base < end; base += kTilePts) {
+            asm volatile("" ::: "memory");   // (the weights are read from LDS where they are used)
+            const int64_t pt = base + 32 * j + lo;   // this lane's point in a tile
+            // z1 = W1 e
+            v16f z = zero16();
+            product<kLevels>(z, [&](int l) { return W1row[2 * l]; }, [&](int l) { return e[l]; });
+            __syncthreads();   // (the previous tile's reads of Q and R)
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
-                float s = 0.0f;
+                z[r] = fmaxf(z[r], 0.0f);
+                Qout[dfeat(0, r, 0) * kWs] = z[r];
+            }
+            __syncthreads();
+            // z2 = W2 h1
+            v16f y = zero16();
+            product<32>(y, [&](int k) { return W2row[dfeat(k >> 4, k & 15, 0)]; },
+                        [&](int k) { return Qcol[dfeat(k >> 4, k & 15, 0) * kWs]; });
 #pragma unroll
-                for (int o = 0; o < kOut; ++o) s = fmaf(W3[o * kHid + dfeat(u, r, h)], d3[o], s);
-                y[r] = y[r] > 0.0f ? s : 0.0f;
-                if ((r & 3) == 3) __builtin_amdgcn_sched_barrier(0);
+            for (int r = 0; r < 16; ++r) {
+                y[r] = fmaxf(y[r], 0.0f);
+                Rout[dfeat(0, r, 0) * kWs] = y[r];
+            }
+            __syncthreads();
+            // outputs o = wave (and 4 on the first wavefront): each lane sums its
+            // half of the features of two points, the halves meet with a swap
+            for (int o = wave; o < kOut; o += kBlock / 64) {
+                float s0 = 0.0f, s1 = 0.0f;
+                const float* w3 = W3 + o * kHid + 4 * h;
+                const float* hr = R + 4 * h * kWs + lo;
+#pragma unroll
+                for (int k = 0; k < 32; ++k) {
+                    const int c = dfeat(k >> 4, k & 15, 0);
+                    s0 = fmaf(w3[c], hr[c * kWs], s0);
+                    s1 = fmaf(w3[c], hr[c * kWs + 32], s1);
+                    if ((k & 7) == 7) __builtin_amdgcn_sched_barrier(0);
+                }
+                float pa, pb;
+                swap_halves(s0, s1, pa, pb);
+                const float yv = 1.0f / (1.0f + expf(-(pa + pb)));
+                const int64_t i = base + lane;
+                D3[o][lane] = i < a.n ? gy[o * gs + i] * yv * (1.0f - yv) : 0.0f;
+            }
+            __syncthreads();
+            // dW3 += d3 h2^T (16 columns per wavefront); d2 = (W3^T d3) masked
+#pragma unroll
+            for (int k0 = 0; k0 < kTilePts; k0 += 4) {
+                const float av = l16 < kOut ? D3[l16 < kOut ? l16 : 0][k0 + k16] : 0.0f;
+                dw3 = __builtin_amdgcn_mfma_f32_16x16x4f32(av, R[(16 * wave + l16) * kWs + k0 + k16], dw3, 0, 0, 0);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            {
+                float d3[kOut];
+#pragma unroll
+                for (int o = 0; o < kOut; ++o) d3[o] = D3[o][32 * j + lo];
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    float s = 0.0f;
+#pragma unroll
+                    for (int o = 0; o < kOut; ++o) s = fmaf(W3[o * kHid + dfeat(u, r, h)], d3[o], s);
+                    y[r] = y[r] > 0.0f ? s : 0.0f;
+                    if ((r & 3) == 3) __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+            __syncthreads();
+#pragma unroll
+            for (int r = 0; r < 16; ++r) Rout[dfeat(0, r, 0) * kWs] = y[r];
+            __syncthreads();
+            // (the encoding again, a row per wavefront and step, for dW1)
+            float er[kHid / 4];
+            {
+                const int64_t i = base + lane;
+                const float* src = ws + (int64_t)wave * wn + (i < a.n ? i : 0);
+#pragma unroll
+                for (int q = 0; q < kHid / 4; ++q) er[q] = src[(int64_t)(4 * q) * wn];
+                if (i >= a.n) {
+#pragma unroll
+                    for (int q = 0; q < kHid / 4; ++q) er[q] = 0.0f;
+                }
+            }
+            // dW2 += d2 h1^T; d1 = (W2^T d2) masked
+            product<32>(dw2, [&](int k) { return R[(32 * u + lo) * kWs + h + 2 * k]; },
+                        [&](int k) { return Q[(32 * j + lo) * kWs + h + 2 * k]; });
+            v16f g = zero16();
+            product<32>(g, [&](int k) { return W2col[dfeat(k >> 4, k & 15, 0) * kWs]; },
+                        [&](int k) { return Rcol[dfeat(k >> 4, k & 15, 0) * kWs]; });
+            __syncthreads();
+#pragma unroll
+            for (int r = 0; r < 16; ++r) Qout[dfeat(0, r, 0) * kWs] = z[r] > 0.0f ? g[r] : 0.0f;
+#pragma unroll
+            for (int q = 0; q < kHid / 4; ++q) R[(4 * q + wave) * kWs + lane] = er[q];
+            __syncthreads();
+            // (the run's next tile, or the first of the workgroup's next run)
+            const int64_t next = base + kTilePts < end ? base + kTilePts : (run + (int)gridDim.x) * run_pts;
+            if (next < a.n) fetch(next);
+            // dW1 += d1 e^T; feature gradients W1^T d1: features 2l and 2l + 1 sit
+            // in registers r, r + 1 (r even) of one lane, one float2 per level
+            product<32>(dw1, [&](int k) { return Q[(32 * u + lo) * kWs + h + 2 * k]; },
+                        [&](int k) { return R[(32 * j + lo) * kWs + h + 2 * k]; });
+            g = zero16();
+            product<32>(g, [&](int k) { return W1col[dfeat(k >> 4, k & 15, 0) * kWs]; },
+                        [&](int k) { return Qcol[dfeat(k >> 4, k & 15, 0) * kWs]; });
+            if (pt < a.n) {
+#pragma unroll
+                for (int r = 0; r < 16; r += 2)
+                    fgrad[(int64_t)(dfeat(u, r, h) >> 1) * wn + pt] = make_float2(g[r], g[r + 1]);
             }
         }
-        __syncthreads();
+        __builtin_amdgcn_sched_barrier(0);
+        float* out = part + (int64_t)run * kWeights;
+        int at = dfeat(u, 0, h) * kHid + 32 * j + lo;
+        asm volatile("" : "+v"(at));   // (no address of the partial kept across the tiles)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) Rout[dfeat(0, r, 0) * kWs] = y[r];
-        __syncthreads();
-        // (the encoding again, a row per wavefront and step, for dW1)
-        float er[kHid / 4];
-        {
-            const int64_t i = base + lane;
-            const float* src = ws + (int64_t)wave * wn + (i < a.n ? i : 0);
-#pragma unroll
-            for (int q = 0; q < kHid / 4; ++q) er[q] = src[(int64_t)(4 * q) * wn];
-            if (i >= a.n) {
-#pragma unroll
-                for (int q = 0; q < kHid / 4; ++q) er[q] = 0.0f;
-            }
+        for (int r = 0; r < 16; ++r) {
+            out[at + dfeat(0, r, 0) * kIn] = dw1[r];
+            out[at + kW1 + dfeat(0, r, 0) * kHid] = dw2[r];
         }
-        // dW2 += d2 h1^T; d1 = (W2^T d2) masked
-        product<32>(dw2, [&](int k) { return R[(32 * u + lo) * kWs + h + 2 * k]; },
-                    [&](int k) { return Q[(32 * j + lo) * kWs + h + 2 * k]; });
-        v16f g = zero16();
-        product<32>(g, [&](int k) { return W2col[dfeat(k >> 4, k & 15, 0) * kWs]; },
-                    [&](int k) { return Rcol[dfeat(k >> 4, k & 15, 0) * kWs]; });
-        __syncthreads();
 #pragma unroll
-        for (int r = 0; r < 16; ++r) Qout[dfeat(0, r, 0) * kWs] = z[r] > 0.0f ? g[r] : 0.0f;
-#pragma unroll
-        for (int q = 0; q < kHid / 4; ++q) R[(4 * q + wave) * kWs + lane] = er[q];
-        __syncthreads();
-        if (base + step < a.n) fetch(base + step);
-        // dW1 += d1 e^T; feature gradients W1^T d1: features 2l and 2l + 1 sit
-        // in registers r, r + 1 (r even) of one lane, one float2 per level
-        product<32>(dw1, [&](int k) { return Q[(32 * u + lo) * kWs + h + 2 * k]; },
-                    [&](int k) { return R[(32 * j + lo) * kWs + h + 2 * k]; });
-        g = zero16();
-        product<32>(g, [&](int k) { return W1col[dfeat(k >> 4, k & 15, 0) * kWs]; },
-                    [&](int k) { return Qcol[dfeat(k >> 4, k & 15, 0) * kWs]; });
-        if (pt < a.n) {
-#pragma unroll
-            for (int r = 0; r < 16; r += 2)
-                fgrad[(int64_t)(dfeat(u, r, h) >> 1) * wn + pt] = make_float2(g[r], g[r + 1]);
-        }
+        for (int r = 0; r < 4; ++r)
+            if (4 * k16 + r < kOut) out[kW1 + kW2 + (4 * k16 + r) * kHid + 16 * wave + l16] = dw3[r];
     }
-    float* out = part + (int64_t)blockIdx.x * kWeights;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-        out[dfeat(u, r, h) * kIn + 32 * j + lo] = dw1[r];
-        out[kW1 + dfeat(u, r, h) * kHid + 32 * j + lo] = dw2[r];
-    }
-#pragma unroll
-    for (int r = 0; r < 4; ++r)
-        if (4 * k16 + r < kOut) out[kW1 + kW2 + (4 * k16 + r) * kHid + 16 * wave + l16] = dw3[r];
 }
 
 // The forward pass in the same layout: the two hidden layers on the matrix
@@ -805,9 +815,9 @@ __global__ __launch_bounds__(kBlock) void k_hg_table_grad(TableGrad g) {
     }
 }
 
-// gparams[weights] += the workgroups' partials: eight threads per weight sum
-// an eighth of the workgroups each, in order and in double, and the eighths
-// are added in order.
+// gparams[weights] += the runs' partials: eight threads per weight sum an
+// eighth of the runs each, in order and in double, and the eighths are added in
+// order.
 constexpr int kRedParts = 8, kRedCols = kBlock / kRedParts;
 __global__ __launch_bounds__(kBlock) void k_hg_wreduce(const float* __restrict__ part, int n_parts,
                                                        float* __restrict__ gparams) {
@@ -873,16 +883,24 @@ int mlp_blocks(int64_t n) {
     return (int)std::min<int64_t>(grid_points(n), (int64_t)cus * 3);
 }
 
-// Workgroups of k_hg_backward: one per 64 points, up to the two that a CU
-// holds (one: 1.23 against 1.01 ms on 1,843,200 points).  Their partials take
-// 8512 floats each, less than the 261 rows of the workspace that 64 points
-// leave unused.
-int backward_blocks(int64_t n) {
-    int dev = 0, cus = 256;
-    if (hipGetDevice(&dev) == hipSuccess)
-        (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-    return (int)std::min<int64_t>((n + kTilePts - 1) / kTilePts, (int64_t)cus * 2);
-}
+// The runs of tiles whose weight gradients k_hg_backward sums in single
+// precision: at most kRunTiles tiles (2,048 points) each, and for a larger point
+// set as few as keep kRunSlots workgroups (two for each of the 256 CUs; one per
+// CU: 1.23 against 1.01 ms on 1,843,200 points) at the same number of runs.
+// They depend on the number of points only, not on the device, and so do the
+// sums.  A run's partial takes 8512 floats, less than the 261 rows of the
+// workspace that its first 64 points leave unused.
+constexpr int kRunTiles = 32, kRunSlots = 512;
+struct BackwardRuns {
+    int tiles;   // of one run
+    int runs;
+    explicit BackwardRuns(int64_t n) {
+        const int64_t t = (n + kTilePts - 1) / kTilePts;
+        const int64_t each = (t + (int64_t)kRunSlots * kRunTiles - 1) / ((int64_t)kRunSlots * kRunTiles);
+        tiles = (int)((t + kRunSlots * each - 1) / (kRunSlots * each));
+        runs = (int)((t + tiles - 1) / tiles);
+    }
+};
 
 // Lanes per slot of a level's table gather: the power of two nearest above
 // a quarter of the mean list length of the level's (light, nonempty) slots,
@@ -1109,13 +1127,13 @@ static int hashgrid_backward(fipt_hashgrid_plan plan, const float* params, const
                     (long long)fipt_hashgrid_workspace_floats(n));
     hipStream_t st = (hipStream_t)stream;
     // workspace: the encoding (64 n floats), the feature gradients (64 n), the
-    // workgroups' weight-gradient partials
+    // runs' weight-gradient partials
     float2* fgrad = reinterpret_cast<float2*>(workspace + (int64_t)kIn * n);
     float* part = workspace + (int64_t)(kIn + kFeatGradRows) * n;
-    const int blocks = backward_blocks(n);
+    const BackwardRuns br(n);
     if (!saved && (rc = launch_encode(a, workspace, n, st))) return rc;
-    hipLaunchKernelGGL(k_hg_backward, dim3(blocks), dim3(kBlock), 0, st, a, grad_material, gm_stride, workspace, n,
-                       fgrad, part);
+    hipLaunchKernelGGL(k_hg_backward, dim3(std::min(br.runs, kRunSlots)), dim3(kBlock), 0, st, a, grad_material,
+                       gm_stride, workspace, n, fgrad, part, br.tiles, br.runs);
     rc = check_hg("hashgrid_backward");
     if (rc) return rc;
     TableGrad tg;
@@ -1139,7 +1157,7 @@ static int hashgrid_backward(fipt_hashgrid_plan plan, const float* params, const
     if (first > 0) hipLaunchKernelGGL(k_hg_table_grad, dim3((unsigned)first), dim3(kBlock), 0, st, tg);
     rc = check_hg("hashgrid_table_grad");
     if (rc) return rc;
-    hipLaunchKernelGGL(k_hg_wreduce, dim3(kWeights / kRedCols), dim3(kBlock), 0, st, part, blocks, grad_params);
+    hipLaunchKernelGGL(k_hg_wreduce, dim3(kWeights / kRedCols), dim3(kBlock), 0, st, part, br.runs, grad_params);
     return check_hg("hashgrid_wreduce");
 }
 
