@@ -1092,6 +1092,32 @@ int fipt_hashgrid_forward(const float* params, const float* pos, int64_t pos_str
     return check_hg("hashgrid_forward");
 }
 
+int fipt_hashgrid_forward_scratch(const float* params, const float* pos, int64_t pos_stride, int64_t n,
+                                  const float* bmin_host, const float* bmax_host, float* material,
+                                  int64_t mat_stride, float* scratch, int64_t scratch_floats,
+                                  void* stream) {
+    clear_error();
+    HgArgs a;
+    int rc = make_args(params, pos, pos_stride, n, bmin_host, bmax_host, a);
+    if (rc) return rc;
+    if (!material || !scratch) return fail(FIPT_EINVAL, "NULL argument");
+    if (mat_stride < n) return fail(FIPT_EINVAL, "mat_stride < n");
+    if (scratch_floats < kIn)
+        return fail(FIPT_EINVAL, "scratch holds %lld floats, at least %d needed", (long long)scratch_floats, kIn);
+    const int64_t run = std::min(n, scratch_floats / kIn);
+    for (int64_t first = 0; first < n; first += run) {
+        a.pos = pos + first;
+        a.n = std::min(run, n - first);
+        rc = launch_encode(a, scratch, a.n, (hipStream_t)stream);
+        if (rc) return rc;
+        hipLaunchKernelGGL(k_hg_mlp, dim3(mlp_blocks(a.n)), dim3(kBlock), 0, (hipStream_t)stream, params, scratch,
+                           a.n, a.n, material + first, mat_stride);
+        rc = check_hg("hashgrid_forward_scratch");
+        if (rc) return rc;
+    }
+    return FIPT_OK;
+}
+
 int fipt_hashgrid_forward_save(const float* params, const float* pos, int64_t pos_stride, int64_t n,
                                const float* bmin_host, const float* bmax_host, float* material,
                                int64_t mat_stride, float* workspace, int64_t workspace_floats,
