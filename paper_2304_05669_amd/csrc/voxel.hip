@@ -129,15 +129,14 @@ __device__ __forceinline__ void pool_large(const int32_t* __restrict__ start, co
 __global__ __launch_bounds__(kBlock) void k_voxel_pool(const int32_t* __restrict__ start,
                                                        const int32_t* __restrict__ order,
                                                        int64_t n_vox, const int32_t* __restrict__ large,
-                                                       int32_t n_large,
+                                                       int32_t n_large, int32_t large_blocks,
                                                        const float* __restrict__ obs, int64_t os,
                                                        float* __restrict__ out, int64_t cs) {
     __shared__ float s_q[kWaves][3][kShare];
-    const int32_t large_blocks = (n_large + kWaves - 1) / kWaves;
     if ((int32_t)blockIdx.x < large_blocks) {
         const int wave = threadIdx.x >> 6;
-        const int32_t i = (int32_t)blockIdx.x * kWaves + wave;
-        if (i < n_large) pool_large(start, order, obs, os, out, cs, large[i], threadIdx.x & 63, s_q[wave]);
+        for (int64_t i = (int64_t)blockIdx.x * kWaves + wave; i < n_large; i += (int64_t)large_blocks * kWaves)
+            pool_large(start, order, obs, os, out, cs, large[i], threadIdx.x & 63, s_q[wave]);
         return;
     }
     const int64_t step = (int64_t)(gridDim.x - large_blocks) * kBlock;
@@ -484,8 +483,12 @@ int fipt_voxel_pool(fipt_voxel_plan pl, const float* observed, int64_t obs_strid
     if (!pl || !observed || !cache) return fail(FIPT_EINVAL, "NULL argument");
     if (obs_stride < pl->n) return fail(FIPT_EINVAL, "obs_stride < the plan's pixel count");
     if (cache_stride < pl->n_vox) return fail(FIPT_EINVAL, "cache_stride < res^3");
-    hipLaunchKernelGGL(k_voxel_pool, dim3((unsigned)((pl->n_large + kWaves - 1) / kWaves + grid_for(pl->n_vox))),
-                       dim3(kBlock), 0, (hipStream_t)stream, pl->start, pl->order, pl->n_vox, pl->large, pl->n_large,
+    // (a wavefront for each large voxel, up to the 32 workgroups per CU that
+    // bound every launch here: of 2^32 threads and more HIP runs only some,
+    // without an error)
+    const int32_t large_blocks = pl->n_large ? grid_for((int64_t)pl->n_large * 64) : 0;
+    hipLaunchKernelGGL(k_voxel_pool, dim3((unsigned)(large_blocks + grid_for(pl->n_vox))), dim3(kBlock), 0,
+                       (hipStream_t)stream, pl->start, pl->order, pl->n_vox, pl->large, pl->n_large, large_blocks,
                        observed, obs_stride, cache, cache_stride);
     return check_voxel("voxel_pool");
 }
