@@ -35,12 +35,13 @@ using dev::v3;
 constexpr int kBlock = 64;
 // The wavefronts a CU holds at once (4 per SIMD): every wavefront starts with
 // a point of its own, so a workgroup that waited for a place would keep its
-// point until the others are nearly done.  Four per SIMD (128 VGPRs, two of
-// them spilled) measured faster than three (131, none) and five (96, 44
-// spilled): 34.6 against 42.3 and 39.1 ms on 76,800 points of the room at 64
-// samples per lobe.
-constexpr int kGridWavesPerCu = 16;
-#define FIPT_REFINE_OCCUPANCY __attribute__((amdgpu_waves_per_eu(4, 8)))
+// point until the others are nearly done.  Four per SIMD (128 VGPRs) measured
+// faster than three (154) and five (96, 44 spilled): 33.4 against 36.1 and 39.1
+// ms on 76,800 points of the room at 64 samples per lobe.  Where three per SIMD
+// hold all points at once, each wavefront has one point and its own latency is
+// what counts: the schedule with more registers and loads in flight takes 1.73
+// against 2.01 ms on 2,000 points, and 2.97 against 2.41 on 4,000.
+constexpr int kGridWavesPerCu = 16, kFewWavesPerCu = 12;
 constexpr int kListBlock = 256;        // triangles per block of the emitter compaction
 constexpr int kScanThreads = 1024;
 
@@ -817,10 +818,12 @@ __device__ void refine_point_spec(const RefineArgs& A, int64_t p, int lane, uint
     }
 }
 
-// The chunked layout (any K) or the per-lane paths (K <= kRefillMaxK), one
-// instance each, so that each gets its own register allocation.
-template <bool CHUNKED>
-__global__ __launch_bounds__(kBlock) FIPT_REFINE_OCCUPANCY void k_refine(RefineArgs A, int32_t* counters) {
+// The chunked layout (any K) or the per-lane paths (K <= kRefillMaxK), these
+// for few points and for many, one instance each, so that each gets its own
+// register allocation.
+template <bool CHUNKED, bool FEW>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(FEW ? 2 : 4, FEW ? 3 : 8))) void k_refine(
+    RefineArgs A, int32_t* counters) {
     __shared__ int32_t s_stack[kStackSize * kBlock];
     const int lane = threadIdx.x & 63;
     const uint32_t stack = dev::lds_address(s_stack + threadIdx.x);
@@ -875,10 +878,12 @@ int launch_refine(const BakeLaunch& b, const RefineLaunch& r, int32_t* counters,
     hipStream_t st = (hipStream_t)stream;
     zero_point_counters(counters, b.n, blocks, stream);
     // the per-lane paths give every output slot its own lane (3 + 6K <= 64)
-    if (A.b.K <= kRefillMaxK)
-        hipLaunchKernelGGL(k_refine<false>, dim3((unsigned)blocks), dim3(kBlock), 0, st, A, counters);
+    if (A.b.K <= kRefillMaxK && b.n <= (int64_t)cus * kFewWavesPerCu)
+        hipLaunchKernelGGL((k_refine<false, true>), dim3((unsigned)blocks), dim3(kBlock), 0, st, A, counters);
+    else if (A.b.K <= kRefillMaxK)
+        hipLaunchKernelGGL((k_refine<false, false>), dim3((unsigned)blocks), dim3(kBlock), 0, st, A, counters);
     else
-        hipLaunchKernelGGL(k_refine<true>, dim3((unsigned)blocks), dim3(kBlock), 0, st, A, counters);
+        hipLaunchKernelGGL((k_refine<true, false>), dim3((unsigned)blocks), dim3(kBlock), 0, st, A, counters);
     return check("refine");
 }
 
