@@ -677,10 +677,15 @@ __global__ __launch_bounds__(kAdjBlock) void k_grid_adjoint_sums(GridPlanDev P,
         for (int ch = 0; ch < C; ++ch) acc[ch][i] = 0;
         bad[i] = 0;
     }
-    // (a wavefront takes every fourth column: neighbours are mostly of one
-    // cell and their integer adds meet in the same nodes: 53.2 -> 48.3 us at
-    // 1.84 M points on 128^3 nodes, 14.0 -> 12.9 us at 8,192 on 32^3)
-    const int32_t ci = unit.y + (tid & 63) * (kAdjBlock / 64) + (tid >> 6);
+    // As many wavefronts as the unit's columns fill, each taking every 2nd, 3rd
+    // or 4th: neighbours are mostly of one cell, and in one wavefront their
+    // integer adds meet in the same nodes.  The whole step, identity tone map:
+    // 8,192 points on 32^3 nodes 21.8 us with a run of columns per wavefront and
+    // 20.8 with a stride, 60,000 on 64^3 24.7 and 23.2, 1,843,200 on 128^3 146.3
+    // and 140.9, 300,000 on 64^3 37.0 and 37.4; four wavefronts for any unit took
+    // 16.4 instead of 15.0 on 1,000 points of 32^3, whose units have few columns.
+    const int32_t waves = (unit.z - unit.y + 63) >> 6;
+    const int32_t ci = (tid >> 6) < waves ? unit.y + (tid & 63) * waves + (tid >> 6) : unit.z;
     const bool live = ci < unit.z;
     float v[8][C];
     float m[C];
