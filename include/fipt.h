@@ -572,7 +572,8 @@ int64_t fipt_hashgrid_workspace_floats(int64_t n);
  * (a stable radix sort per level); returns once the plan is complete.
  * 1 <= n < 2^28; bmin_host < bmax_host (host float [3]).  The plan owns
  * device memory (12 bytes per point, 8 per nonzero (point, corner) per
- * level, at most 8 per point and level, and at most 4 MB per level). */
+ * level, at most 8 per point and level, and for the slots' ranges and lists
+ * 2 MB per level and at most 4 MB more). */
 int fipt_hashgrid_plan_create(const float* pos, int64_t pos_stride, int64_t n, const float* bmin_host,
                               const float* bmax_host, void* stream, fipt_hashgrid_plan* out);
 int fipt_hashgrid_plan_destroy(fipt_hashgrid_plan plan);

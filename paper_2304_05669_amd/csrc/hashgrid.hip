@@ -9,16 +9,17 @@
 // Parameters, one float array: tables [32][2^19][2], then W1 [64][64],
 // W2 [64][64], W3 [5][64] (row = output).
 //
-// Forward: one lane per point for the encoding (the 256 table gathers per
-// point, 8 vertices x 32 levels of 8 bytes, are the memory traffic; the
-// tables, 134 MB, live in HBM and the MALL) and the two hidden layers on the
-// matrix cores over the wavefront's 64 points (see below), the weights in
-// LDS; the five outputs on the vector ALUs.
+// Forward: the encoding (256 table gathers per point, 8 vertices x 32 levels of
+// 8 bytes) as a kernel of its own, one level of all points before the next, so
+// that a level's 4 MB table stays in each XCD's L2; then the two hidden layers
+// on the matrix cores over a wavefront's 64 points (see below), the weights in
+// LDS, and the five outputs on the vector ALUs.  Without room for the encoding
+// one kernel does both, a lane going through all levels of its point.
 //
-// Backward: each workgroup recomputes the forward pass of 64 points from their
+// Backward: a workgroup recomputes the forward pass of 64 points from their
 // encoding, back-propagates through the MLP, stores the per-level feature
 // gradients (W1^T d1, two per level) and accumulates the weight gradients of
-// its points, all on the matrix cores; a last kernel adds the workgroups'
+// its run of points, all on the matrix cores; a last kernel adds the runs'
 // weight gradients in order.  The table gradient is a gather: a plan built
 // once for the point set lists, per level, every (point, corner) with a
 // nonzero trilinear weight sorted by table slot (then point, then corner),
