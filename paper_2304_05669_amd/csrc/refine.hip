@@ -33,15 +33,23 @@ using dev::V3;
 using dev::v3;
 
 constexpr int kBlock = 64;
-// The wavefronts a CU holds at once (4 per SIMD): every wavefront starts with
-// a point of its own, so a workgroup that waited for a place would keep its
-// point until the others are nearly done.  Four per SIMD (128 VGPRs) measured
-// faster than three (154) and five (96, 44 spilled): 33.4 against 36.1 and 39.1
-// ms on 76,800 points of the room at 64 samples per lobe.  Where three per SIMD
-// hold all points at once, each wavefront has one point and its own latency is
-// what counts: the schedule with more registers and loads in flight takes 1.73
-// against 2.01 ms on 2,000 points, and 2.97 against 2.41 on 4,000.
+// The wavefronts a CU holds at once, four or three per SIMD: every wavefront
+// starts with a point of its own, so a workgroup that waited for a place would
+// keep its point until the others are nearly done.  Four per SIMD (128 VGPRs)
+// measured faster on many points than three (154) and five (96, 44 spilled):
+// 33.4 against 36.1 and 39.1 ms on 76,800 points of the room at 64 samples per
+// lobe.  With three, a point takes about 3/4 of the time, in a schedule with
+// more loads in flight, which is better where the points fill whole rounds of
+// them (ms in the room, 64 samples per lobe, three against four: 2,000 points
+// 1.73 and 2.01, 4,096 3.05 and 2.33, 6,144 3.54 and 3.93, 8,192 4.67 and 4.47,
+// 9,000 4.89 and 5.15, 12,288 6.70 and 6.46; beyond that rounds blur).
 constexpr int kGridWavesPerCu = 16, kFewWavesPerCu = 12;
+bool three_per_simd(int64_t n, int64_t cus) {
+    const int64_t r3 = (n + kFewWavesPerCu * cus - 1) / (kFewWavesPerCu * cus);
+    // (a point per CU beyond a round of four is hidden behind its longest points)
+    const int64_t r4 = std::max<int64_t>(1, (n - cus + kGridWavesPerCu * cus - 1) / (kGridWavesPerCu * cus));
+    return r3 <= 3 && 3 * r3 < 4 * r4;
+}
 constexpr int kListBlock = 256;        // triangles per block of the emitter compaction
 constexpr int kScanThreads = 1024;
 
@@ -818,9 +826,9 @@ __device__ void refine_point_spec(const RefineArgs& A, int64_t p, int lane, uint
     }
 }
 
-// The chunked layout (any K) or the per-lane paths (K <= kRefillMaxK), these
-// for few points and for many, one instance each, so that each gets its own
-// register allocation.
+// The chunked layout (any K) or the per-lane paths (K <= kRefillMaxK), at three
+// wavefronts per SIMD (FEW) or four, one instance each, so that each gets its
+// own register allocation.
 template <bool CHUNKED, bool FEW>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(FEW ? 2 : 4, FEW ? 3 : 8))) void k_refine(
     RefineArgs A, int32_t* counters) {
@@ -873,17 +881,20 @@ int launch_refine(const BakeLaunch& b, const RefineLaunch& r, int32_t* counters,
     int dev = 0, cus = 256;
     if (hipGetDevice(&dev) == hipSuccess)
         (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-    int64_t blocks = std::min<int64_t>(b.n, (int64_t)cus * kGridWavesPerCu);
+    const bool few = three_per_simd(b.n, cus);
+    int64_t blocks = std::min<int64_t>(b.n, (int64_t)cus * (few ? kFewWavesPerCu : kGridWavesPerCu));
     blocks = std::max<int64_t>(kXcdCount, (blocks + kXcdCount - 1) / kXcdCount * kXcdCount);
     hipStream_t st = (hipStream_t)stream;
     zero_point_counters(counters, b.n, blocks, stream);
     // the per-lane paths give every output slot its own lane (3 + 6K <= 64)
-    if (A.b.K <= kRefillMaxK && b.n <= (int64_t)cus * kFewWavesPerCu)
-        hipLaunchKernelGGL((k_refine<false, true>), dim3((unsigned)blocks), dim3(kBlock), 0, st, A, counters);
-    else if (A.b.K <= kRefillMaxK)
-        hipLaunchKernelGGL((k_refine<false, false>), dim3((unsigned)blocks), dim3(kBlock), 0, st, A, counters);
-    else
-        hipLaunchKernelGGL((k_refine<true, false>), dim3((unsigned)blocks), dim3(kBlock), 0, st, A, counters);
+    const dim3 grid((unsigned)blocks), block(kBlock);
+    if (A.b.K <= kRefillMaxK) {
+        if (few) hipLaunchKernelGGL((k_refine<false, true>), grid, block, 0, st, A, counters);
+        else hipLaunchKernelGGL((k_refine<false, false>), grid, block, 0, st, A, counters);
+    } else {
+        if (few) hipLaunchKernelGGL((k_refine<true, true>), grid, block, 0, st, A, counters);
+        else hipLaunchKernelGGL((k_refine<true, false>), grid, block, 0, st, A, counters);
+    }
     return check("refine");
 }
 

@@ -1,7 +1,7 @@
-"""The refinement's form for few points (at most 12 per CU) and the one for
-more give the same bits: the points of a launch one above the line, and the same
-points in launches at the line and below it; and as the chunked form above 10
-roughness levels is untouched by the line, it agrees across it as well."""
+"""The refinement at three wavefronts per SIMD and at four gives the same bits:
+launches on both sides of each size at which the form changes (12 points per CU,
+17, 24, 33 and 36), against the same points of the largest launch; for the
+per-lane paths and for the chunked form above 10 roughness levels."""
 import pytest
 import torch
 
@@ -12,8 +12,9 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("levels", [6, 11])
-def test_forms_agree_across_the_line(levels):
-    line = 12 * torch.cuda.get_device_properties(0).multi_processor_count
+def test_forms_agree_across_the_lines(levels):
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    lines = [12 * cus, 17 * cus, 24 * cus, 33 * cus, 36 * cus]
     sc = synth.serving_rooms(seed=0, n_cams=1, which=[0])[0]
     scene = fipt.Scene(sc.verts, sc.tris, device=0)
     try:
@@ -24,15 +25,15 @@ def test_forms_agree_across_the_line(levels):
         sigma = [0.05 + 0.9 * i / levels for i in range(levels)]
         grid = torch.rand((5, 8, 8, 8), generator=torch.Generator().manual_seed(2)).cuda()
         box = (sc.bmin.tolist(), sc.bmax.tolist())
-        first = (planes.shape[1] - line - 1) // 2
+        first = (planes.shape[1] - lines[-1] - 1) // 2
 
         def refine(n):
             return fipt.fipt_refine(scene, planes[:, first:first + n].contiguous(), tri[first:first + n].contiguous(),
-                                    8, 8, sigma, 7, grid, *box)
+                                    4, 4, sigma, 7, grid, *box)
 
-        above = refine(line + 1)
-        assert float(above.abs().max()) > 0
-        for n in (line, line - 1, 65):
-            assert torch.equal(refine(n), above[:, :n].contiguous()), n
+        full = refine(lines[-1] + 1)
+        assert float(full.abs().max()) > 0
+        for n in [65] + [k + more for k in lines for more in (0, 1)]:
+            assert torch.equal(refine(n), full[:, :n].contiguous()), n
     finally:
         scene.destroy()
