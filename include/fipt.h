@@ -553,9 +553,9 @@ int fipt_hashgrid_forward(const float* params, const float* pos, int64_t pos_str
                           int64_t mat_stride, void* stream);
 
 /* fipt_hashgrid_forward with `scratch` (device, at least 64 floats) for the
- * points' hash encoding, 64 floats per point: faster, because the points are
- * encoded level by level, in runs of scratch_floats / 64 points.  The result is
- * fipt_hashgrid_forward's bit for bit.  Calls that share a scratch must not
+ * points' hash encoding, 64 floats per point, in runs of scratch_floats / 64
+ * points: faster where encoding a run level by level is (most sizes), the same
+ * elsewhere.  The result is fipt_hashgrid_forward's bit for bit.  Calls that share a scratch must not
  * overlap.  Asynchronous on `stream`. */
 int fipt_hashgrid_forward_scratch(const float* params, const float* pos, int64_t pos_stride, int64_t n,
                                   const float* bmin_host, const float* bmax_host, float* material,

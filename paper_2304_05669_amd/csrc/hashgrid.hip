@@ -368,8 +368,9 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 8))) 
 
 // The forward pass in the same layout: the two hidden layers on the matrix
 // cores, the five outputs summed per half-wave on the vector ALUs.
-// For callers without room for the encoding; k_hg_encode and k_hg_mlp, which
-// keep it, take 1.2 against 1.67 ms on 1,843,200 points.
+// For callers without room for the encoding and for the sizes where it is the
+// faster form (see one_kernel_forward); k_hg_encode and k_hg_mlp, which keep the
+// encoding, take 1.2 against 1.67 ms on 1,843,200 points.
 __global__ __launch_bounds__(kBlock) void k_hg_forward(HgArgs a, float* __restrict__ out, int64_t os) {
     __shared__ float w[kLdsW];
     load_weights(a.params, w);
@@ -876,12 +877,25 @@ int launch_encode(const HgArgs& a, float* ws, int64_t wn, hipStream_t st) {
     return check_hg("hashgrid_encode");
 }
 
-// Workgroups of k_hg_mlp: one per 256 points, up to the three that a CU holds.
-int mlp_blocks(int64_t n) {
+int device_cus() {
     int dev = 0, cus = 256;
     if (hipGetDevice(&dev) == hipSuccess)
         (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-    return (int)std::min<int64_t>(grid_points(n), (int64_t)cus * 3);
+    return cus;
+}
+
+// Workgroups of k_hg_mlp: one per 256 points, up to the three that a CU holds.
+int mlp_blocks(int64_t n) { return (int)std::min<int64_t>(grid_points(n), (int64_t)device_cus() * 3); }
+
+// Whether inference runs k_hg_forward although there is room for the encoding:
+// from three quarters of a workgroup per CU to the three that a CU holds it is
+// one round, whose latency grows with the workgroups per CU only, while the
+// encoding by levels takes its time per point from the first (us, one kernel
+// against two: 40,000 points 98 and 86, 50,000 98 and 98, 65,536 99 and 113,
+// 120,000 128 and 161, 196,608 178 and 196, 200,000 228 and 211).
+bool one_kernel_forward(int64_t n) {
+    const int64_t groups = grid_points(n), cus = device_cus();
+    return 4 * groups > 3 * cus && groups <= 3 * cus;
 }
 
 // The runs of tiles whose weight gradients k_hg_backward sums in single
@@ -1109,6 +1123,12 @@ int fipt_hashgrid_forward_scratch(const float* params, const float* pos, int64_t
     for (int64_t first = 0; first < n; first += run) {
         a.pos = pos + first;
         a.n = std::min(run, n - first);
+        if (one_kernel_forward(a.n)) {
+            hipLaunchKernelGGL(k_hg_forward, dim3(grid_points(a.n)), dim3(kBlock), 0, (hipStream_t)stream, a,
+                               material + first, mat_stride);
+            if ((rc = check_hg("hashgrid_forward_scratch"))) return rc;
+            continue;
+        }
         rc = launch_encode(a, scratch, a.n, (hipStream_t)stream);
         if (rc) return rc;
         hipLaunchKernelGGL(k_hg_mlp, dim3(mlp_blocks(a.n)), dim3(kBlock), 0, (hipStream_t)stream, params, scratch,

@@ -51,3 +51,13 @@ def test_without_memory(monkeypatch):
 
     monkeypatch.setattr(fipt, "hashgrid_scratch", no_memory)
     assert torch.equal(fipt.fipt_hashgrid_forward(params, pos, LO, HI), _plain(params, pos))
+
+
+@pytest.mark.parametrize("groups", [(3, 4, 0), (3, 4, 1), (3, 1, 0), (3, 1, 1)])
+def test_forms_agree_where_they_change(groups):
+    """At the sizes between which one kernel does the whole pass: a multiple of
+    the CUs in workgroups of 256 points, and a point more."""
+    num, den, more = groups
+    n = 256 * num * torch.cuda.get_device_properties(0).multi_processor_count // den + more
+    params, pos = _params(), _points(n, 4)
+    assert torch.equal(fipt.fipt_hashgrid_forward(params, pos, LO, HI), _plain(params, pos))
