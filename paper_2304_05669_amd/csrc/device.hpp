@@ -678,10 +678,10 @@ __device__ __forceinline__ int64_t wave_uniform(int64_t v) {
 // load before it takes from another share: an atomic on a shared line costs
 // about 12 ns, one after another, so eight counters in one line, tried in
 // turn by every wavefront that ran out, bounded every launch of short points
-// (4096 points of 448 samples in the 20-triangle box: 454 us, now 63; 10,007
-// points of 139 samples in a 75k-triangle room: 667 us, now 220).  A launch
-// with no more points than wavefronts touches no counter.  Each point's result does
-// not depend on which wavefront bakes it.
+// (4096 points of 448 samples in the 20-triangle box: 455 us, now 57; 10,007
+// points of 139 samples in a 75,440-triangle room: 670 us, now 207).  A launch
+// with no more points than wavefronts touches no counter.  Each point's result
+// does not depend on which wavefront bakes it.
 //
 // The wavefront's place in the hand-out is one word (the traversal loop is
 // short of scalar registers): which shares' counters may still have points

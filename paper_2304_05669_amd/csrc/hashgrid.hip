@@ -160,8 +160,8 @@ __device__ __forceinline__ void load_weights(const float* __restrict__ params, f
 // products that decide the masks (z1, z2) are formed as in the forward pass.
 // Bound by the single-precision matrix rate: 200 products of 64 cycles per
 // wavefront and 64 points, 0.6 ms on the room's 1,843,200 points.  It takes
-// 1.01 ms there (two wavefronts per SIMD, 69 KB of LDS per workgroup, and the
-// barriers between the products), with its reduction 1.02; as a per-point
+// 1.02 ms there (two wavefronts per SIMD, 69 KB of LDS per workgroup, and the
+// barriers between the products), with its reduction 1.04; as a per-point
 // kernel that wrote every activation and layer gradient (1.3 KB per point) and
 // a split-K kernel that read them back it took 1.20 + 0.55 + 0.11 ms.
 constexpr int kTilePts = 64;

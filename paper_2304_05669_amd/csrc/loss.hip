@@ -51,7 +51,7 @@ struct SigmaTable {
 // because the reciprocals and the power start from the hardware's
 // approximations and need one step of high order: the masked loss of 600,001
 // points 44 -> 23 us, the fused grid loss of 1,843,200 points 150 -> 111 us
-// (99 without a tone map: what is left is the planes' memory traffic).
+// (82 without a tone map: the planes' memory traffic).
 
 // 1 / v: the hardware reciprocal (relative error d of about 2^-23) and one
 // step of third order (error d^3).

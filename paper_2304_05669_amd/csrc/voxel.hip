@@ -198,8 +198,7 @@ __global__ __launch_bounds__(kBlock) void k_voxel_words(uint4* __restrict__ word
 }
 
 // The same for R a multiple of 4 and planes of 16-byte alignment (256^3: 38 us
-// against 91): one
-// wavefront takes four bricks side by side, lane 16 b + r the row r of four
+// against 91): one wavefront takes four bricks side by side, lane 16 b + r the row r of four
 // voxels of brick b with one load per plane (64 contiguous bytes per row of
 // the four, where the general form reads 16), and the rows' bits meet by
 // four steps of 16-lane rotations.
